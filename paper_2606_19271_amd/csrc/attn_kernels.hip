@@ -55,6 +55,7 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+typedef __attribute__((address_space(3))) u32x2 lds_u32x2;
 typedef __attribute__((address_space(3))) char lds_char;
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -89,7 +90,22 @@ struct Geo {
   static constexpr int kVStages = 3;                     // V_j in stage j % 3
   static constexpr int kVRing = 0;                       // byte offset of the V ring
   static constexpr int kKRing = kVStages * kVTile;       // byte offset of the K ring
-  static constexpr int kLds = kKStages * kKTile + kVStages * kVTile;
+  static constexpr int kRings = kKStages * kKTile + kVStages * kVTile;
+  // Q staging of the prologue: 32 rows of each wave, in the K stage that no prologue fetch fills
+  // and the space after the rings (and, for the one wave that does not fit there, in the last V
+  // stage, unused until the first vector step as well).
+  static constexpr int kQWave = 32 * D * 2;              // bytes of one wave's query rows
+  static constexpr int kQBase = kKRing + (kKStages - 1) * kKTile;
+  static constexpr int kQFit = 7;                        // waves staged from kQBase on
+  static constexpr int kQLast = kVRing + (kVStages - 1) * kVTile;
+  // Output staging of the epilogue, after the rings: 32 rows of 128 bytes per wave, padded by one
+  // 16-byte chunk (both sides of the transposition then spread over the banks).
+  static constexpr int kORow = 128 + 16;
+  static constexpr int kOBase = kRings;
+  static constexpr int kOWave = 32 * kORow;
+  static constexpr int kLdsQ = kQBase + kQFit * kQWave;
+  static constexpr int kLdsO = kOBase + kWaves * kOWave;
+  static constexpr int kLds = kLdsQ > kLdsO ? kLdsQ : kLdsO;
   static constexpr int kGroupWaves = kWaves / 2;
   static constexpr int kKDma = kKTile / 1024;            // DMA instructions per K tile (17 / 18)
   static constexpr int kVDma = kVTile / 1024;            // per V tile (16 / 16)
@@ -103,6 +119,8 @@ struct Geo {
   static constexpr int kDmaEvery = 4;
   static_assert(kKTile % 1024 == 0 && kVTile % 1024 == 0 && kVDma % kGroupWaves == 0, "DMA split");
   static_assert(kVStages * kVTile <= 65536, "V addresses must fit the DS immediate");
+  static_assert(kLds <= 160 * 1024, "LDS of a CU");
+  static_assert(kQWave <= kVTile && kQFit == kWaves - 1, "the last wave's queries fit a V stage");
   __host__ __device__ static constexpr int vswz(int r) {
     return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | ((r >> 2) & 3));
   }
@@ -309,10 +327,9 @@ struct NoIssue {
 // (OR & 0x40004000) != 0 flags a tile whose weights are not all below 2.
 // issue(0 .. kIssue - 1) is called in order, instruction i at the start of pair step
 // i * kEvery (kEvery = 0: all at the start): the vector step's K/V DMA instructions go there.
-template <int NT, bool kMasked, int kIssue = 0, int kEvery = 0, typename Issue = NoIssue>
+template <int NT, int kIssue = 0, int kEvery = 0, typename Issue = NoIssue>
 __device__ __forceinline__ unsigned exp_pack(const f32x16 (&s)[NT / 2], bf16x8 (&p)[NT],
-                                             float m_c, float c, int keys_valid, int hb,
-                                             Issue&& issue = Issue{}) {
+                                             float m_c, float c, Issue&& issue = Issue{}) {
   static_assert(kEvery * (kIssue - 1) < NT * 4, "issue points");
   unsigned any = 0;
 #pragma unroll
@@ -335,11 +352,6 @@ __device__ __forceinline__ unsigned exp_pack(const f32x16 (&s)[NT / 2], bf16x8 (
       float x0 = s[t >> 1][8 * (t & 1) + m], x1 = s[t >> 1][8 * (t & 1) + m + 1];
       float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(x0, c, -m_c));
       float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(x1, c, -m_c));
-      if (kMasked) {
-        int key0 = 16 * t + 8 * (m >> 2) + 4 * hb + (m & 3);
-        if (key0 >= keys_valid) e0 = 0.0f;
-        if (key0 + 1 >= keys_valid) e1 = 0.0f;
-      }
       f32x2 e = {e0, e1};
       bf16x2 pb = __builtin_convertvector(e, bf16x2);
       p[t][m] = pb[0];
@@ -366,25 +378,27 @@ __device__ __forceinline__ unsigned exp_pack(const f32x16 (&s)[NT / 2], bf16x8 (
 // that here, in the rare slow path of the vector step, keeps the matrix step free of branches.
 constexpr float kBias = 39.0f;
 
+// Which tile of an item a vector step works on.  The first one's maximum is taken at once: its
+// weights against m_c = -inf are all infinite, so an attempt with the running maximum never holds
+// (skipping it saves 620 clocks per group at d = 128 and 1200 at d = 64, of an item's two first
+// vector steps).  The last one is masked: its keys past the segment's end score -inf, so their
+// weights are exactly 0 (c > 0, see softmax_factor).
+enum TileKind { kFirstTile = 0, kInnerTile = 1, kLastTile = 2 };
+
 // issue(0 .. kIssue - 1): instructions to spread over the tile's exp work (see exp_pack); all
 // of them are issued once, on every path.
-template <int D, bool kMasked, int kIssue, typename Issue>
+template <int D, int kKind, int kIssue, typename Issue>
 __device__ __forceinline__ void softmax_tile(f32x16 (&s)[Geo<D>::kBN / 32],
                                              bf16x8 (&p)[Geo<D>::kBN / 16], float& m_c,
                                              f32x16 (&o)[D / 32], f32x4 (&l)[2], float c,
                                              int keys_valid, int lane, Issue&& issue) {
   constexpr int kBN = Geo<D>::kBN;
   const int hb = lane >> 5;
-  if (!kMasked) {
-    const unsigned any =
-        exp_pack<kBN / 16, false, kIssue, Geo<D>::kDmaEvery>(s, p, m_c, c, kBN, hb, issue);
+  if (kKind == kInnerTile) {
+    const unsigned any = exp_pack<kBN / 16, kIssue, Geo<D>::kDmaEvery>(s, p, m_c, c, issue);
     if (__builtin_amdgcn_ballot_w64((any & 0x40004000u) != 0) == 0) return;
   }
-  if (kMasked) {
-#pragma unroll
-    for (int i = 0; i < kIssue; ++i) issue(i);
-  }
-  if (kMasked) {
+  if (kKind == kLastTile) {
 #pragma unroll
     for (int kb = 0; kb < kBN / 32; ++kb)
 #pragma unroll
@@ -401,15 +415,18 @@ __device__ __forceinline__ void softmax_tile(f32x16 (&s)[Geo<D>::kBN / 32],
   mt = half_max(mt);
   // c >= 0, so the max commutes with the scaling
   const float m_new = fmaxf(m_c, __builtin_fmaf(mt, c, kBias));
-  const float alpha = __builtin_amdgcn_exp2f(m_c - m_new);  // 0 on the first tile (m_c = -inf)
+  if (kKind != kFirstTile) {  // nothing is accumulated before the first tile
+    const float alpha = __builtin_amdgcn_exp2f(m_c - m_new);  // 0 where m_c = -inf
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+    l[0] *= alpha;
+    l[1] *= alpha;
+  }
   m_c = m_new;
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-  l[0] *= alpha;
-  l[1] *= alpha;
-  exp_pack<kBN / 16, kMasked>(s, p, m_c, c, keys_valid, hb);
+  if (kKind == kInnerTile) exp_pack<kBN / 16>(s, p, m_c, c);
+  else exp_pack<kBN / 16, kIssue, Geo<D>::kDmaEvery>(s, p, m_c, c, issue);
 }
 
 // Lane offsets (bytes, relative to the tile's first row in global memory) of one wave's share
@@ -483,12 +500,55 @@ __device__ __forceinline__ void dma_v_one(__amdgpu_buffer_rsrc_t rv, int key0, i
                                            16, voff[u] + key0 * row_bytes, 0, 0, 0);
 }
 
+// Q's fragments through LDS.  A wave's 32 query rows are fetched by LDS DMA, whole rows at a time
+// (an instruction covers 1 KiB of consecutive row bytes), and read back as MFMA B operands.  Loaded
+// straight into registers, each 16-byte-per-lane instruction would touch 32 rows: a call of one
+// 256-key item takes 10.6 us at d = 128 and 8.6 at d = 64 that way, 9.5 and 8.1 this way, and one
+// of 84 items of 1560 keys 32.8 against 31.5.  Chunk c of row r is stored at chunk position
+// c ^ qswz(r), so that the 16 rows one b128 read touches per 16 lanes fall on distinct banks.
+template <int D>
+__device__ __forceinline__ constexpr int qswz(int r) {
+  return D == 128 ? r & 15 : (r >> 1) & 7;
+}
+template <int D>
+__device__ __forceinline__ lds_char* q_stage(lds_char* lds, int wave) {
+  using G = Geo<D>;
+  return lds + (wave < G::kQFit ? G::kQBase + wave * G::kQWave : G::kQLast);
+}
+template <int D>
+__device__ __forceinline__ void dma_q(__amdgpu_buffer_rsrc_t rq, int q0, int row_bytes,
+                                      lds_char* stage, int lane) {
+  using G = Geo<D>;
+#pragma unroll
+  for (int n = 0; n < G::kQWave / 1024; ++n) {
+    const int row = (64 * n + lane) / G::kChunks;
+    const int chunk = (lane % G::kChunks) ^ qswz<D>(row);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rq, (lds_void*)(stage + 1024 * n), 16,
+                                             (q0 + row) * row_bytes + chunk * 16, 0, 0, 0);
+  }
+}
+// The wave's Q fragments from its stage (fragment kk: query lane & 31, channels 16kk + 8hb + 0..7);
+// flip: sign bits to invert.
+template <int D>
+__device__ __forceinline__ void read_q(const lds_char* stage, bf16x8 (&qf)[D / 16], unsigned flip,
+                                       int lane) {
+  const int row = lane & 31, hb = lane >> 5;
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) {
+    const u32x4 raw = *(const lds_u32x4*)(stage + row * D * 2 + (((2 * kk + hb) ^ qswz<D>(row)) << 4));
+    qf[kk] = __builtin_bit_cast(bf16x8, raw ^ u32x4{flip, flip, flip, flip});
+  }
+}
+
 // Waits until at most N of this wave's vector-memory operations are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_vmem() {
   static_assert(N >= 0 && N < 16, "vmcnt field");
   __builtin_amdgcn_s_waitcnt(0x0F70 | N);  // gfx9 encoding: expcnt and lgkmcnt left open
 }
+
+// Waits until this wave's LDS operations are done (gfx9 encoding: vmcnt and expcnt left open).
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
 // Workgroup barrier without a memory fence (the waits before it are explicit); the empty asm
 // statements keep the compiler from moving memory accesses across it.
@@ -561,7 +621,7 @@ __device__ __forceinline__ void m_step(const lds_char* __restrict__ kt, const ld
 template <int D, int kMode>
 __device__ __forceinline__ void write_result(const Item& it, const Out& out,
                                              const f32x16 (&oacc)[D / 32], float l_tot, float m_c,
-                                             int H, int qrow, int hb);
+                                             int H, int q0, lds_char* stage, int lane);
 
 //
 // kActive = false is the same schedule for a wave whose 32 queries all lie past the segment's end
@@ -579,7 +639,6 @@ __device__ __forceinline__ void run_item_group(const Item& it, const __bf16* __r
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int gw = wave & (G::kGroupWaves - 1);  // wave inside its group
-  const int hb = lane >> 5, col = lane & 31;
   const int row_bytes = H * D * 2;
   // element offsets of (first query, h) and (first key, h); byte ranges of the segment's rows
   const int64_t qbase = (it.q_start * H + it.h) * D;
@@ -625,18 +684,6 @@ __device__ __forceinline__ void run_item_group(const Item& it, const __bf16* __r
   constexpr int kFetchAhead = kGroupB ? 2 : 3;  // tiles between a fetch and its first reader
   constexpr int kFetchWait = kGroupB ? G::kVDmaPerWave : G::kKDmaMin;  // fewest per wave
 
-  // Q fragments (B operand of S^T = K Q^T): query col of this wave, channels 16kk + 8hb + 0..7
-  const int qrow = it.q_begin + 32 * wave + col;
-  bf16x8 qf[D / 16];
-#pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) {
-    u32x4 raw = {};
-    if constexpr (kActive)
-      raw = __builtin_amdgcn_raw_buffer_load_b128(rq, qrow * row_bytes + (2 * kk + hb) * 16, 0, 0);
-    if (negate_q) raw ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
-    qf[kk] = __builtin_bit_cast(bf16x8, raw);
-  }
-
   f32x16 oacc[D / 32];
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) oacc[db] = f32x16{};
@@ -653,32 +700,40 @@ __device__ __forceinline__ void run_item_group(const Item& it, const __bf16* __r
   // vector step j: fetch tile j + kFetchAhead (a V tile into stage vst2 = (j + 2) % 3), its
   // instructions spread over the softmax S_j -> P_j, wait for the fetch of the previous vector
   // step, read the first K fragments of
-  // M(j + 1); kMasked on the last tile only, which has no M(j + 1) S product.  The barrier that
+  // M(j + 1) (the last tile has no M(j + 1) S product).  The barrier that
   // closes the step opens the next iteration, so the loop's branch is taken before it and the
   // matrix step that follows the barrier starts with its first MFMA.
-  auto vstep = [&](int j, int vst2, auto masked) {
-    constexpr bool kMasked = decltype(masked)::value;
+  auto vstep = [&](int j, int vst2, auto kind) {
+    constexpr int kKind = decltype(kind)::value;
     auto issue = [&](int u) { fetch_one(j + kFetchAhead, vst2, u); };
     if constexpr (kActive) {
-      softmax_tile<D, kMasked, kSpread>(s, p, m_c, oacc, lacc, c, kMasked ? last_keys : kBN, lane,
-                                        issue);
+      softmax_tile<D, kKind, kSpread>(s, p, m_c, oacc, lacc, c, last_keys, lane, issue);
     } else {
 #pragma unroll
       for (int u = 0; u < kSpread; ++u) issue(u);
     }
     fetch_rest(j + kFetchAhead);
     wait_vmem<kFetchWait>();
-    if (kActive && !kMasked) k_preread<D>(ktile((j + 1) & 3), kp, lane);
+    if (kActive && kKind != kLastTile) k_preread<D>(ktile((j + 1) & 3), kp, lane);
   };
-  using Full = std::false_type;
-  using Last = std::true_type;
+  using First = std::integral_constant<int, kFirstTile>;
+  using Inner = std::integral_constant<int, kInnerTile>;
+  using Last = std::integral_constant<int, kLastTile>;
 
-  // prologue: tiles 0 .. kFetchAhead - 1 of this group's operand, complete before anyone reads
-  // them
+  // prologue: tiles 0 .. kFetchAhead - 1 of this group's operand and the wave's query rows, complete
+  // before anyone reads them.  Q is read out of its stage before the barrier: the first vector step
+  // refills the ring stages it sits in.
   fetch(0, 0);
+  if constexpr (kActive) dma_q<D>(rq, it.q_begin + 32 * wave, row_bytes, q_stage<D>(lds, wave), lane);
   fetch(1, 1);
   if (!kGroupB) fetch(2, 2);
   wait_vmem<0>();
+  __asm__ volatile("" ::: "memory");
+  bf16x8 qf[D / 16] = {};
+  if constexpr (kActive) {
+    read_q<D>(q_stage<D>(lds, wave), qf, negate_q ? 0x80008000u : 0u, lane);
+    wait_lds();
+  }
   block_sync();
   if constexpr (kActive) k_preread<D>(ktile(0), kp, lane);
   if (kGroupB) block_sync();  // group B starts one step behind
@@ -693,10 +748,10 @@ __device__ __forceinline__ void run_item_group(const Item& it, const __bf16* __r
   if (ntiles == 1)
     vstep(0, 2, Last{});
   else
-    vstep(0, 2, Full{});
+    vstep(0, 2, First{});
   // ---- tiles 1..: K_j sits in stage j % 4; V_{j-1} in vs = (j + 2) % 3, where V_{j+2} goes next
   int vs = 0;
-  auto tile = [&](int j, auto masked) {
+  auto tile = [&](int j, auto kind) {
     block_sync();  // closes V(j - 1)
     if constexpr (kActive) {
       __builtin_amdgcn_s_setprio(1);
@@ -704,11 +759,11 @@ __device__ __forceinline__ void run_item_group(const Item& it, const __bf16* __r
       __builtin_amdgcn_s_setprio(0);
     }
     block_sync();
-    vstep(j, vs, masked);
+    vstep(j, vs, kind);
     vs = vs == 2 ? 0 : vs + 1;
   };
   int j = 1;
-  for (; j < ntiles - 1; ++j) tile(j, Full{});
+  for (; j < ntiles - 1; ++j) tile(j, Inner{});
   if (j == ntiles - 1) tile(j, Last{});
   // ---- M(ntiles): the last product, V_{ntiles-1} in stage (ntiles - 1) % 3 = vs now
   block_sync();  // closes V(ntiles - 1)
@@ -720,35 +775,61 @@ __device__ __forceinline__ void run_item_group(const Item& it, const __bf16* __r
   wait_vmem<0>();  // the fetches past the end must land before the workgroup leaves
 
   if constexpr (kActive)
-    write_result<D, kMode>(it, out, oacc, lacc[0][0] + lacc[1][0], m_c, H, qrow, hb);
+    write_result<D, kMode>(it, out, oacc, lacc[0][0] + lacc[1][0], m_c, H, it.q_begin + 32 * wave,
+                           lds + G::kOBase + wave * G::kOWave, lane);
 }
 
-// The epilogue of one wave: O = O / l for its 32 query rows, and the row's natural log-sum-exp
-// lse = (m_c + log2 l) ln 2 (m_c is in log2 units of the scaled scores).  l_tot = 0 marks an
-// item without keys: O = 0 and lse = -inf.  Rows past the segment end are dropped by the
-// descriptors' range checks.
+// The epilogue of one wave: O = O / l for its 32 query rows (the first is q0, relative to the
+// segment), and the row's natural log-sum-exp lse = (m_c + log2 l) ln 2 (m_c is in log2 units of the
+// scaled scores).  l_tot = 0 marks an item without keys: O = 0 and lse = -inf.  Rows past the
+// segment end are dropped by the descriptors' range checks.
+//
+// A lane holds 4-channel pieces of one query, so stores straight from the registers touch 32 rows
+// with 16 bytes each, and the CU's address path takes about 75 clocks for each of a workgroup's 128
+// (d = 128): from the last product to the last store 9000 clocks of every item, as long as four
+// key tiles.  The rows go through the wave's own LDS stage instead, 128 bytes of each at a time,
+// and leave as 16-byte stores of eight whole 128-byte lines: 3500 clocks.
 template <int D, int kMode>
 __device__ __forceinline__ void write_result(const Item& it, const Out& out,
                                              const f32x16 (&oacc)[D / 32], float l_tot, float m_c,
-                                             int H, int qrow, int hb) {
+                                             int H, int q0, lds_char* stage, int lane) {
+  using G = Geo<D>;
+  const int col = lane & 31, hb = lane >> 5;
+  const int qrow = q0 + col;
   const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
   const float lse = l_tot > 0.0f ? (m_c + log2f(l_tot)) * kLn2 : -INFINITY;
   const uint32_t lse_bytes = ((uint32_t)(it.q_len - 1) * (uint32_t)H + 1) * 4;
+  // After the transposition lane i holds bytes 16 (i % 8) .. + 15 of the pass's 128 of the rows
+  // i / 8 + 8 u.
+  const int orow = lane >> 3, ochunk = lane & 7;
+  lds_char* const put = stage + col * G::kORow;
+  const lds_char* const get = stage + orow * G::kORow + ochunk * 16;
+  // the stage's accesses of a wave are in order in the LDS; the empty asm keeps them so here
+  auto in_order = [] { __asm__ volatile("" ::: "memory"); };
   if (kMode == kFinal) {
     const int row_bytes = H * D * 2;
     const uint32_t q_bytes = (uint32_t)(it.q_len - 1) * (uint32_t)row_bytes + D * 2;
     __amdgpu_buffer_rsrc_t ro = make_rsrc(out.o + (it.q_start * H + it.h) * D, q_bytes);
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int d0 = 0; d0 < D / 32; d0 += 2) {  // two 32-channel blocks per pass
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        f32x4 x = {oacc[db][4 * g4] * inv, oacc[db][4 * g4 + 1] * inv, oacc[db][4 * g4 + 2] * inv,
-                   oacc[db][4 * g4 + 3] * inv};
-        bf16x4 b = __builtin_convertvector(x, bf16x4);
-        u32x2 w = __builtin_bit_cast(u32x2, b);
-        const int ch = 32 * db + 8 * g4 + 4 * hb;  // first of 4 channels
-        __builtin_amdgcn_raw_buffer_store_b64(w, ro, qrow * row_bytes + ch * 2, 0, 0);
-      }
+      for (int db = d0; db < d0 + 2; ++db)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          f32x4 x = {oacc[db][4 * g4] * inv, oacc[db][4 * g4 + 1] * inv, oacc[db][4 * g4 + 2] * inv,
+                     oacc[db][4 * g4 + 3] * inv};
+          bf16x4 b = __builtin_convertvector(x, bf16x4);
+          const int ch = 32 * (db - d0) + 8 * g4 + 4 * hb;  // first of 4 channels
+          *(lds_u32x2*)(put + ch * 2) = __builtin_bit_cast(u32x2, b);
+        }
+      in_order();
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        __builtin_amdgcn_raw_buffer_store_b128(*(const lds_u32x4*)(get + 8 * u * G::kORow), ro,
+                                               (q0 + orow + 8 * u) * row_bytes + d0 * 64 + ochunk * 16,
+                                               0, 0);
+      in_order();
+    }
     if (out.lse != nullptr && hb == 0) {
       __amdgpu_buffer_rsrc_t rl = make_rsrc(out.lse + it.q_start * H + it.h, lse_bytes);
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(lse), rl, qrow * H * 4, 0, 0);
@@ -758,19 +839,26 @@ __device__ __forceinline__ void write_result(const Item& it, const Out& out,
     const uint32_t o_bytes = ((uint32_t)(it.q_len - 1) * (uint32_t)H + 1) * D * 4;
     __amdgpu_buffer_rsrc_t rpo = make_rsrc(out.part_o + ((slab + it.q_start) * H + it.h) * D, o_bytes);
     // Byte offsets of fp32 rows reach twice the bf16 ones: with (q_len + 256) * H * D * 2 < 2^31
-    // (the host's size limit) and qrow < q_len + 256 they stay below 2^32, so they are formed in
+    // (the host's size limit) and rows < q_len + 256 they stay below 2^32, so they are formed in
     // unsigned 32-bit arithmetic (the buffer offset register is unsigned) without wrapping.
-    const uint32_t row_off = (uint32_t)qrow * (uint32_t)(H * D) * 4u;
+    const uint32_t row_step = (uint32_t)(H * D) * 4u;
+    const uint32_t off0 = (uint32_t)(q0 + orow) * row_step + (uint32_t)ochunk * 16u;
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int db = 0; db < D / 32; ++db) {  // one 32-channel block per pass
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         f32x4 x = {oacc[db][4 * g4] * inv, oacc[db][4 * g4 + 1] * inv, oacc[db][4 * g4 + 2] * inv,
                    oacc[db][4 * g4 + 3] * inv};
-        const uint32_t ch = 32 * db + 8 * g4 + 4 * hb;
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rpo,
-                                               __builtin_bit_cast(int, row_off + ch * 4u), 0, 0);
+        *(lds_u32x4*)(put + (8 * g4 + 4 * hb) * 4) = __builtin_bit_cast(u32x4, x);
       }
+      in_order();
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        __builtin_amdgcn_raw_buffer_store_b128(*(const lds_u32x4*)(get + 8 * u * G::kORow), rpo,
+                                               __builtin_bit_cast(int, off0 + 8u * u * row_step + 128u * db),
+                                               0, 0);
+      in_order();
+    }
     if (hb == 0) {
       __amdgpu_buffer_rsrc_t rl = make_rsrc(out.part_lse + (slab + it.q_start) * H + it.h, lse_bytes);
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(lse), rl, qrow * H * 4, 0, 0);
@@ -846,16 +934,15 @@ __device__ __forceinline__ void run_thin_item(const Item& it, const __bf16* __re
   };
 
   // Q fragments (B operand of the 16x16x32 S MFMAs): query i16 of block qb, channels
-  // 32 kk + 8 g + 0..7
+  // 32 kk + 8 g + 0..7.  Loaded between the first two fetches, and its sign flipped after the wait
+  // (as in the main schedule, no use of Q delays a fetch).
   const int qrow = it.q_begin + 16 * qb + i16;
-  bf16x8 qf[D / 32];
+  fetch(0, 0);
+  u32x4 qraw[D / 32];
 #pragma unroll
-  for (int kk = 0; kk < D / 32; ++kk) {
-    u32x4 raw = __builtin_amdgcn_raw_buffer_load_b128(rq, qrow * row_bytes + (32 * kk + 8 * g) * 2,
-                                                      0, 0);
-    if (negate_q) raw ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
-    qf[kk] = __builtin_bit_cast(bf16x8, raw);
-  }
+  for (int kk = 0; kk < D / 32; ++kk)
+    qraw[kk] = __builtin_amdgcn_raw_buffer_load_b128(rq, qrow * row_bytes + (32 * kk + 8 * g) * 2, 0, 0);
+  fetch(1, 1);
   // LDS offsets inside a tile: the K row of this lane in 16-key block t is 16 (4 t + kq) + i16;
   // the V rows of its transpose reads are 16 (4 t + kq) + 4 g + 0..3, and the swizzle depends on
   // the row mod 16 only, so the offset of channel block cb is the same for every block t.
@@ -874,9 +961,12 @@ __device__ __forceinline__ void run_thin_item(const Item& it, const __bf16* __re
   const int ntiles = it.ntiles;
   const int last_keys = min(kBN, it.k_len - (it.tile_begin + ntiles - 1) * kBN);
 
-  fetch(0, 0);
-  fetch(1, 1);
   wait_vmem<kWait>();
+  const unsigned qflip = negate_q ? 0x80008000u : 0u;
+  bf16x8 qf[D / 32];
+#pragma unroll
+  for (int kk = 0; kk < D / 32; ++kk)
+    qf[kk] = __builtin_bit_cast(bf16x8, qraw[kk] ^ u32x4{qflip, qflip, qflip, qflip});
   block_sync();
   int st = 0;  // stage of tile j
   for (int j = 0; j < ntiles; ++j) {
@@ -1049,8 +1139,8 @@ __device__ __forceinline__ void run_item(const Item& it, const __bf16* __restric
     f32x16 zero[D / 32];
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) zero[db] = f32x16{};
-    write_result<D, kMode>(it, out, zero, 0.0f, -INFINITY, H, it.q_begin + 32 * wave + (lane & 31),
-                           lane >> 5);
+    write_result<D, kMode>(it, out, zero, 0.0f, -INFINITY, H, it.q_begin + 32 * wave,
+                           (lds_char*)smem + Geo<D>::kOBase + wave * Geo<D>::kOWave, lane);
     return;
   }
   if (kThin && it.q_len - it.q_begin <= kThinQueries) {
@@ -1280,11 +1370,19 @@ plan_kernel(const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, 
 // ---------------------------------------------------------------------------------------------
 // host-side launchers
 
+// The factor of the scores in the exponent, |scale| log2(e) (a negative scale flips Q's signs).  It
+// is kept positive, so that a masked score of -inf has weight 0: scale 0 takes the least subnormal,
+// whose product with any finite score, below 4.8e-7, is less than half an ulp of m_c = kBias.
+static float softmax_factor(float scale) {
+  const float c = fabsf(scale) * kLog2e;
+  return c > 0.0f ? c : 1.401298464e-45f;
+}
+
 template <int D>
 static hipError_t launch_dense_d(const DenseArgs& a, hipStream_t st) {
   const int nq = (a.L + kBM - 1) / kBM;
   const int total = a.B * a.H * nq;
-  const float c = fabsf(a.scale) * kLog2e;
+  const float c = softmax_factor(a.scale);
   const int tail = a.L % kBM;
   auto kern = tail != 0 && tail <= kThinQueries ? attn_dense_kernel<D, true>
                                                 : attn_dense_kernel<D, false>;
@@ -1304,7 +1402,7 @@ static hipError_t launch_packed_d(const PackedArgs& a, hipStream_t st) {
     if (e != hipSuccess) return e;
   }
   const int64_t grid = packed_grid_bound(a.total_q, a.nseq, a.H, a.n_split);
-  const float c = fabsf(a.scale) * kLog2e;
+  const float c = softmax_factor(a.scale);
   const int neg = a.scale < 0.0f ? 1 : 0;
   Out out{(__bf16*)a.o, a.lse, a.part_o, a.part_lse, a.total_q, 0};
   if (a.n_split == 1) {
