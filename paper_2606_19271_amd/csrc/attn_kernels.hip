@@ -32,10 +32,13 @@
 //    tile's maximum taken and the O accumulator rescaled.  Keeping a stale maximum is exact in
 //    real arithmetic (the final division by the running sum cancels the common factor), so for
 //    ordinary inputs the per-tile max reduction and the O rescale disappear.
+//  * A call with fewer items than a quarter of the CUs runs in 64-query items instead, whose key tiles
+//    are split over the eight waves (run_small_item), with the same results bit for bit.
 //  * Scheduling: the launch has one workgroup per item; blockIdx is remapped so that the 32
 //    workgroups resident at once on one XCD (the hardware deals workgroups to the 8 XCDs
 //    round robin) take 32 consecutive query tiles of the same head and share its K/V in that
-//    XCD's L2.  For packed batches a planning kernel first orders segments longest first.
+//    XCD's L2.  Packed batches run their segments longest first: up to 64 segments are ordered by
+//    every wave itself (WavePlan), larger batches by a planning kernel.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -180,6 +183,11 @@ struct Out {
   float* part_lse;
   int64_t tq;  // query rows of the whole call (one split's slab is tq x H rows)
   int split;   // key range of this item (kPartial)
+};
+
+// What every segment's offsets of a packed call are checked against.
+struct PackedSizes {
+  int max_q, max_k, total_q, total_k;
 };
 
 constexpr float kLn2 = 0.6931471805599453f;
@@ -1127,6 +1135,442 @@ __device__ __forceinline__ void run_thin_item(const Item& it, const __bf16* __re
   }
 }
 
+// ---- Small grids: 64-query items, every K/V tile shared by the eight waves.
+//
+// With fewer 256-query items than CUs a call is one chain of key tiles, each as long as a matrix
+// step and a vector step of a whole wave, while most of the chip idles.  Here a workgroup takes 64
+// queries (two blocks of 32) and splits a key tile's work over its waves instead:
+//  * Waves 0-3, the producers, compute the scores and weights: a score block is 32 keys x 32
+//    queries, an accumulator as in the main schedule.  At d = 128 producer w has keys
+//    32 (w & 1) + 0..31 of query block w >> 1, at d = 64 keys 32 w + 0..31 of both query blocks.
+//    The bf16 weights go to LDS as the fragments that the PV product reads (double-buffered).
+//  * Waves 4-7, the consumers, accumulate O one tile later: at d = 128 consumer c has channels
+//    32 c + 0..31 of both query blocks, at d = 64 channels 32 (c & 1) + 0..31 of query block c >> 1.
+//    One consumer per query block sums its weights (row_sums).
+// Each SIMD holds one producer and one consumer, so the exponentials run under the other's MFMAs.
+// One barrier per tile.  The producers fetch K (K_{j+3} in phase j), the consumers V (V_{j+1}), into
+// rings of three stages; each wave waits for its previous phase's fetch before the barrier.
+//
+// Every score, weight, product and sum is formed by the same instructions in the same order as in
+// run_item_group -- the softmax's decisions are taken per 32 queries and key tile there too -- so the
+// results are the same bit for bit, and the choice between the two may depend on the whole call.
+// A tile whose maximum has to be taken (the first, the last, or one with a weight of 2 or more)
+// exchanges the blocks' maxima through LDS and takes one barrier more (two for the third kind).
+//
+// With all of a call's items resident, a key tile takes 0.57 us at d = 128 and 0.7 us at d = 64 (1300
+// and 1600 clocks), where a 256-query item takes 0.97 and 1.5.  The LDS bounds it: the weights are
+// written once and read by two or four waves, each K fragment feeds one or two MFMAs instead of
+// eight waves' worth of queries, V is read in 64-bit pieces, and the fetches write 33 KiB a tile.
+template <int D>
+struct SmallGeo {
+  using G = Geo<D>;
+  static constexpr int kKB = G::kBN / 32;                // 32-key blocks per tile (2 / 4)
+  static constexpr int kNT = G::kBN / 16;                // 16-key steps per tile (4 / 8)
+  static constexpr int kUnits = kKB / 2;                 // score blocks of a producer (1 / 2)
+  static constexpr int kQB = D / 64;                     // query blocks of a consumer (2 / 1)
+  static constexpr int kPBlock = kNT * 1024;             // weights of one query block and tile
+  static constexpr int kP = G::kRings;                   // weights: [2 buffers][2 query blocks]
+  static constexpr int kMax = kP + 4 * kPBlock;          // float [2 query blocks][kKB][32]
+  static constexpr int kFlag = kMax + 2 * kKB * 32 * 4;  // uint [2 buffers]
+  static constexpr int kSum = kFlag + 16;                // float [2 query blocks][32]
+  static constexpr int kLds = kSum + 2 * 32 * 4;
+  // epilogue: O rows of the item, over the rings
+  static constexpr int kORow16 = D * 2 + 16, kORow32 = D * 4 + 16;
+  static_assert(kSmallTile * kORow32 <= kP, "output stage");
+  static_assert(2 * G::kQWave <= 4 * kPBlock, "query stage");
+  static_assert(kLds <= 160 * 1024, "LDS of a CU");
+};
+
+template <int D, int kMode>
+__device__ __forceinline__ void run_small_item(const Item& it, const __bf16* __restrict__ q,
+                                               const __bf16* __restrict__ k,
+                                               const __bf16* __restrict__ v, const Out& out, int H,
+                                               float c, bool negate_q, char* smem) {
+  using G = Geo<D>;
+  using S = SmallGeo<D>;
+  constexpr int kBN = G::kBN, kNT = S::kNT, kKB = S::kKB;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool producer = wave < kWaves / 2;
+  const int gw = wave & (G::kGroupWaves - 1);
+  const int col = lane & 31, hb = lane >> 5;
+  const int row_bytes = H * D * 2;
+  const int64_t qbase = (it.q_start * H + it.h) * D;
+  const int64_t kbase = (it.k_start * H + it.h) * D;
+  const uint32_t q_bytes = (uint32_t)(it.q_len - 1) * (uint32_t)row_bytes + D * 2;
+  const uint32_t k_bytes = (uint32_t)(it.k_len - 1) * (uint32_t)row_bytes + D * 2;
+  __amdgpu_buffer_rsrc_t rq = make_rsrc(q + qbase, q_bytes);
+  __amdgpu_buffer_rsrc_t rk = make_rsrc(k + kbase, k_bytes);
+  __amdgpu_buffer_rsrc_t rv = make_rsrc(v + kbase, k_bytes);
+  lds_char* const lds = (lds_char*)smem;
+  auto ktile = [&](int stage) { return lds + G::kKRing + stage * G::kKTile; };
+  auto vtile = [&](int stage) { return lds + G::kVRing + stage * G::kVTile; };
+  typedef __attribute__((address_space(3))) float lds_float;
+  typedef __attribute__((address_space(3))) unsigned lds_uint;
+  lds_float* const maxima = (lds_float*)(lds + S::kMax);
+  lds_uint* const flags = (lds_uint*)(lds + S::kFlag);
+  lds_float* const sums = (lds_float*)(lds + S::kSum);
+  auto weights = [&](int buf, int qb) { return lds + S::kP + (2 * buf + qb) * S::kPBlock + lane * 16; };
+  const int ntiles = it.ntiles;
+  const int seg_tiles = (it.k_len + kBN - 1) / kBN;
+  const int last_keys = min(kBN, it.k_len - (it.tile_begin + ntiles - 1) * kBN);
+  auto key0 = [&](int j) { return min(it.tile_begin + j, seg_tiles) * kBN; };  // as in run_item_group
+  // whether tile j's maximum is taken before its weights are formed
+  auto edge = [&](int j) { return j == 0 || j == ntiles - 1; };
+  // Tile j's verdict, read after the barrier of phase j: the query blocks (bit qb) whose weights have
+  // to be formed again with the tile's maximum -- all of an edge tile, else those with a weight of
+  // 2 or more, whose producer has set the buffer's bit (cleared when the tile is settled).
+  auto verdict = [&](int j) { return edge(j) ? 3u : (unsigned)flags[j & 1]; };
+  // the running maximum of block qb's queries with the tile's (maxima: every producer's part)
+  auto raised = [&](float m_c, int qb) {
+    float mt = maxima[qb * kKB * 32 + col];
+#pragma unroll
+    for (int kb = 1; kb < kKB; ++kb) mt = fmaxf(mt, maxima[(qb * kKB + kb) * 32 + col]);
+    return fmaxf(m_c, __builtin_fmaf(mt, c, kBias));
+  };
+
+  // prologue: the queries (64 rows, 1 KiB per instruction, in the weight buffers), K_0 .. K_2, V_0
+  int koff[G::kKDmaMax], voff[G::kVDmaPerWave];
+  if (producer) {
+    dma_offsets_k<D>(gw, lane, row_bytes, koff);
+    dma_k<D>(rk, key0(0), row_bytes, ktile(0), koff, gw);
+  } else {
+    dma_offsets_v<D>(gw, lane, row_bytes, voff);
+  }
+#pragma unroll
+  for (int i = 0; i < 2 * G::kQWave / 1024 / kWaves; ++i) {
+    const int n = wave + kWaves * i;
+    const int row = (64 * n + lane) / G::kChunks;
+    const int chunk = (lane % G::kChunks) ^ qswz<D>(row);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rq, (lds_void*)(lds + S::kP + 1024 * n), 16,
+                                             (it.q_begin + row) * row_bytes + chunk * 16, 0, 0, 0);
+  }
+  if (producer) {
+#pragma unroll
+    for (int m = 1; m < G::kKStages; ++m)
+      dma_k<D>(rk, key0(m), row_bytes, ktile(m), koff, gw);
+  } else {
+    dma_v<D>(rv, key0(0), row_bytes, vtile(0), voff, gw);
+  }
+  if (tid < 2) flags[tid] = 0;
+  wait_lds();
+  wait_vmem<0>();
+  block_sync();
+
+  float l_tot[2] = {0.0f, 0.0f};  // of a summing consumer: its block's row sums
+  float m_c[2] = {-INFINITY, -INFINITY};
+  f32x16 oacc[S::kQB];
+#pragma unroll
+  for (int i = 0; i < S::kQB; ++i) oacc[i] = f32x16{};
+  const int cb = gw & (D / 32 - 1);                // a consumer's channel block
+  const int qb0 = S::kQB == 1 ? gw >> 1 : 0;       // and its first query block
+  const int sum_qb = S::kQB == 1 ? ((gw & 1) == 0 ? qb0 : -1) : (gw < 2 ? gw : -1);
+  if (producer) {
+    const int kb = S::kUnits == 1 ? gw & 1 : gw;
+    const int uq = S::kUnits == 1 ? gw >> 1 : 0;   // query block of unit 0
+    bf16x8 qf[S::kUnits][D / 16];
+#pragma unroll
+    for (int u = 0; u < S::kUnits; ++u)
+      read_q<D>(lds + S::kP + (uq + u) * G::kQWave, qf[u], negate_q ? 0x80008000u : 0u, lane);
+    // K fragments of a tile's score block (fragment kk: channels 16 kk + ..)
+    auto read_k = [&](int stage, bf16x8 (&kf)[D / 16]) {
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk) kf[kk] = *(const lds_bf16x8*)k_frag<D>(ktile(stage), kk, kb, lane);
+    };
+    auto scores = [&](const bf16x8 (&kf)[D / 16], f32x16 (&s)[S::kUnits]) {
+#pragma unroll
+      for (int u = 0; u < S::kUnits; ++u) s[u] = f32x16{};
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk)
+#pragma unroll
+        for (int u = 0; u < S::kUnits; ++u) s[u] = mfma32(kf[kk], qf[u][kk], s[u]);
+    };
+    auto put_weights = [&](const bf16x8 (&p)[2], int u, int buf) {
+      lds_char* const w = weights(buf, uq + u) + 2 * kb * 1024;
+      *(lds_bf16x8*)w = p[0];
+      *(lds_bf16x8*)(w + 1024) = p[1];
+    };
+    auto put_max = [&](const f32x16& s, int u) {
+      float mt = s[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mt = fmaxf(mt, s[r]);
+      mt = half_max(mt);
+      if (hb == 0) maxima[((uq + u) * kKB + kb) * 32 + col] = mt;
+    };
+    // Tile j, whose scores are s, once more if its maximum has to be taken (before phase j + 1)
+    auto settle = [&](int j, unsigned redo, const f32x16 (&s)[S::kUnits]) {
+      if (!edge(j)) {
+#pragma unroll
+        for (int u = 0; u < S::kUnits; ++u)
+          if (redo >> (uq + u) & 1) put_max(s[u], u);
+        wait_lds();
+        block_sync();
+        if (tid == 0) flags[j & 1] = 0;  // every wave has read it
+      }
+#pragma unroll
+      for (int u = 0; u < S::kUnits; ++u)
+        if (redo >> (uq + u) & 1) {
+          m_c[u] = raised(m_c[u], uq + u);
+          const f32x16 s1[1] = {s[u]};
+          bf16x8 p[2];
+          exp_pack<2>(s1, p, m_c[u], c);
+          put_weights(p, u, j & 1);
+        }
+      wait_lds();
+      block_sync();
+    };
+    // Phase j: the weights of tile j from s, the scores of tile j + 1 into next (which holds those of
+    // tile j - 1 on entry) with K_{j+1} from kf, the fragments of K_{j+2} into kn (K_m is complete
+    // before phase m - 2), the fetch of K_{j+4}.
+    auto phase = [&](int j, f32x16 (&s)[S::kUnits], f32x16 (&next)[S::kUnits], bf16x8 (&kf)[D / 16],
+                     bf16x8 (&kn)[D / 16]) {
+      const int buf = j & 1;
+      const int kfrom = key0(j + 4);
+      auto fetch = [&](int u) { dma_k_one<D>(rk, kfrom, row_bytes, ktile(j & 3), koff, gw, u); };
+      if (j > 0) {
+        const unsigned v = verdict(j - 1);
+        read_k((j + 2) & 3, kn);
+        const unsigned redo = __builtin_amdgcn_readfirstlane(v);
+        if (redo != 0) settle(j - 1, redo, next);
+      } else {
+        read_k((j + 2) & 3, kn);
+      }
+      if (edge(j)) {
+#pragma unroll
+        for (int u = 0; u < G::kKDmaMin; ++u) fetch(u);
+        if (j == ntiles - 1) {
+#pragma unroll
+          for (int u = 0; u < S::kUnits; ++u)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              if (32 * kb + 8 * (r >> 2) + 4 * hb + (r & 3) >= last_keys) s[u][r] = -INFINITY;
+        } else {
+          scores(kf, next);
+        }
+#pragma unroll
+        for (int u = 0; u < S::kUnits; ++u) put_max(s[u], u);
+      } else {
+        // one MFMA and two (d = 128) or four score pairs per step, with the barriers to keep the
+        // order: an MFMA that waits for its predecessor's accumulator holds up nothing then
+        bf16x8 p[S::kUnits][2];
+        unsigned any[S::kUnits] = {};
+#pragma unroll
+        for (int u = 0; u < S::kUnits; ++u) next[u] = f32x16{};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (i % 2 == 1) fetch(i / 2);
+          const int mu = i % S::kUnits, mk = i / S::kUnits;
+          next[mu] = mfma32(kf[mk], qf[mu][mk], next[mu]);
+#pragma unroll
+          for (int x = 0; x < S::kUnits; ++x) {
+            const int pair = S::kUnits * i + x, u = pair / 8, r = 2 * (pair % 8);
+            const f32x2 w = {__builtin_amdgcn_exp2f(__builtin_fmaf(s[u][r], c, -m_c[u])),
+                             __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][r + 1], c, -m_c[u]))};
+            const bf16x2 pb = __builtin_convertvector(w, bf16x2);
+            p[u][r / 8][r % 8] = pb[0];
+            p[u][r / 8][r % 8 + 1] = pb[1];
+            any[u] |= __builtin_bit_cast(unsigned, pb);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < S::kUnits; ++u) {
+          put_weights(p[u], u, buf);
+          if (__builtin_amdgcn_ballot_w64((any[u] & 0x40004000u) != 0) != 0 && lane == 0)
+            __hip_atomic_fetch_or(&flags[buf], 1u << (uq + u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+      }
+      dma_k<D, G::kKDmaMin>(rk, kfrom, row_bytes, ktile(j & 3), koff, gw);
+      wait_vmem<G::kKDmaMin>();
+      wait_lds();
+      block_sync();
+    };
+    __builtin_amdgcn_s_setprio(1);  // the longer chain of the two: 2 % (d = 64) to 5 % (d = 128)
+    f32x16 s0[S::kUnits], s1[S::kUnits];
+    bf16x8 k0[D / 16], k1[D / 16];  // K fragments of the next two score blocks
+    read_k(0, k1);
+    scores(k1, s0);
+    read_k(1, k0);
+    wait_lds();
+    block_sync();  // phase 0 refills K_0's stage
+    int j = 0;
+    for (; j + 2 <= ntiles; j += 2) {
+      phase(j, s0, s1, k0, k1);
+      phase(j + 1, s1, s0, k1, k0);
+    }
+    if (j < ntiles) {
+      phase(j, s0, s1, k0, k1);
+      settle(j, 3u, s0);
+    } else {
+      settle(j - 1, 3u, s1);
+    }
+  } else {
+    f32x4 lacc[2] = {};
+    const bf16x8 sel = row_sum_selector(lane);
+    const VOffsets<D> vo(lane);
+    int off[2];
+#pragma unroll
+    for (int r2 = 0; r2 < 2; ++r2) {
+      off[r2] = vo.off[r2][0];
+#pragma unroll
+      for (int db = 1; db < D / 32; ++db)
+        if (cb == db) off[r2] = vo.off[r2][db];
+    }
+    auto settle = [&](int j, unsigned redo) {
+      if (!edge(j)) block_sync();
+#pragma unroll
+      for (int i = 0; i < S::kQB; ++i)
+        if (redo >> (qb0 + i) & 1) {
+          const float m_new = raised(m_c[i], qb0 + i);
+          const float alpha = __builtin_amdgcn_exp2f(m_c[i] - m_new);  // 0 on the first tile
+          m_c[i] = m_new;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
+          if (sum_qb == qb0 + i) {
+            lacc[0] *= alpha;
+            lacc[1] *= alpha;
+          }
+        }
+      wait_lds();
+      block_sync();
+    };
+    // operands of O += V_m P_m
+    bf16x8 p[S::kQB][kNT];
+    bf16x4 vf[kNT][2];
+    auto read_p = [&](int m) {
+#pragma unroll
+      for (int t = 0; t < kNT; ++t)
+#pragma unroll
+        for (int i = 0; i < S::kQB; ++i)
+          p[i][t] = *(const lds_bf16x8*)(weights(m & 1, qb0 + i) + t * 1024);
+    };
+    auto read_v = [&](int stage) {
+      const lds_char* vt = vtile(stage);
+#pragma unroll
+      for (int t = 0; t < kNT; ++t) {
+        const lds_char* base = vt + 16 * t * G::kVRow;
+        vf[t][0] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(base + off[0]));
+        vf[t][1] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(base + off[1]));
+      }
+    };
+    // the product and the weights' row sums; issue(0 .. 3) between the MFMAs
+    auto product = [&](auto issue) {
+#pragma unroll
+      for (int t = 0; t < kNT; ++t) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (t % (kNT / 4) == 0) issue(t / (kNT / 4));
+        const bf16x8 a = {vf[t][0][0], vf[t][0][1], vf[t][0][2], vf[t][0][3],
+                          vf[t][1][0], vf[t][1][1], vf[t][1][2], vf[t][1][3]};
+#pragma unroll
+        for (int i = 0; i < S::kQB; ++i) oacc[i] = mfma32(a, p[i][t], oacc[i]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < S::kQB; ++i)
+        if (sum_qb == qb0 + i) row_sums(sel, p[i], lacc);
+    };
+    int vs = 0;  // stage of V_j
+    block_sync();
+    for (int j = 0; j < ntiles; ++j) {
+      const int next = vs == 2 ? 0 : vs + 1;
+      const int vfrom = key0(j + 1);
+      auto fetch = [&](int u) { dma_v_one<D>(rv, vfrom, row_bytes, vtile(next), voff, gw, u); };
+      if (j > 0) {
+        const unsigned v = verdict(j - 1);
+        read_v(vs == 0 ? 2 : vs - 1);
+        read_p(j - 1);
+        const unsigned redo = __builtin_amdgcn_readfirstlane(v);
+        if (redo != 0) {
+          settle(j - 1, redo);
+          read_p(j - 1);
+        }
+        product(fetch);
+      } else {
+#pragma unroll
+        for (int u = 0; u < G::kVDmaPerWave; ++u) fetch(u);
+      }
+      vs = next;
+      wait_vmem<G::kVDmaPerWave>();
+      wait_lds();
+      block_sync();
+    }
+    settle(ntiles - 1, 3u);
+    read_v(vs == 0 ? 2 : vs - 1);
+    read_p(ntiles - 1);
+    product(NoIssue{});
+    if (sum_qb >= 0) {
+      l_tot[0] = lacc[0][0] + lacc[1][0];
+      if (hb == 0) sums[sum_qb * 32 + col] = l_tot[0];
+    }
+  }
+  // epilogue: normalise into an LDS image of the item's rows, over the rings (every fetch has landed
+  // and every operand is read), then store whole rows
+  wait_vmem<0>();
+  wait_lds();
+  block_sync();
+  constexpr int kEl = kMode == kFinal ? 2 : 4;     // bytes of an output element
+  constexpr int kRow = kMode == kFinal ? S::kORow16 : S::kORow32;
+  if (!producer) {
+#pragma unroll
+    for (int i = 0; i < S::kQB; ++i) {
+      const float l = sums[(qb0 + i) * 32 + col];
+      const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+      lds_char* const put = lds + (32 * (qb0 + i) + col) * kRow + 32 * cb * kEl;
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        f32x4 x = {oacc[i][4 * g4] * inv, oacc[i][4 * g4 + 1] * inv, oacc[i][4 * g4 + 2] * inv,
+                   oacc[i][4 * g4 + 3] * inv};
+        if (kMode == kFinal)
+          *(lds_u32x2*)(put + (8 * g4 + 4 * hb) * 2) =
+              __builtin_bit_cast(u32x2, __builtin_convertvector(x, bf16x4));
+        else
+          *(lds_u32x4*)(put + (8 * g4 + 4 * hb) * 4) = __builtin_bit_cast(u32x4, x);
+      }
+      if (sum_qb == qb0 + i && hb == 0) {
+        const int qrow = it.q_begin + 32 * (qb0 + i) + col;
+        const float lse = l > 0.0f ? (m_c[i] + log2f(l)) * kLn2 : -INFINITY;
+        const uint32_t lse_bytes = ((uint32_t)(it.q_len - 1) * (uint32_t)H + 1) * 4;
+        float* const dst = kMode == kFinal ? out.lse : out.part_lse + (int64_t)out.split * out.tq * H;
+        if (kMode != kFinal || dst != nullptr) {
+          __amdgpu_buffer_rsrc_t rl = make_rsrc(dst + it.q_start * H + it.h, lse_bytes);
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(lse), rl, qrow * H * 4, 0, 0);
+        }
+      }
+    }
+  }
+  wait_lds();
+  block_sync();
+  constexpr int kLanes = D * kEl / 16;             // lanes of a row
+  constexpr int kRows = 64 / kLanes;               // rows of an instruction
+  const uint32_t row_step = (uint32_t)(H * D * kEl);
+  const uint32_t o_bytes = (uint32_t)(it.q_len - 1) * row_step + D * kEl;
+  const int64_t slab = kMode == kFinal ? 0 : (int64_t)out.split * out.tq;
+  __amdgpu_buffer_rsrc_t ro =
+      make_rsrc((kMode == kFinal ? (char*)out.o : (char*)out.part_o) + ((slab + it.q_start) * H + it.h) * D * kEl,
+                o_bytes);
+#pragma unroll
+  for (int n = 0; n < kSmallTile / kRows / kWaves; ++n) {
+    const int row = (wave + kWaves * n) * kRows + lane / kLanes, at = lane % kLanes * 16;
+    // unsigned offsets, as in write_result
+    __builtin_amdgcn_raw_buffer_store_b128(*(const lds_u32x4*)(lds + row * kRow + at), ro,
+                                           __builtin_bit_cast(int, (uint32_t)(it.q_begin + row) * row_step + (uint32_t)at),
+                                           0, 0);
+  }
+}
+
+// An item of kQueries queries without keys: O = 0, lse = -inf.
+template <int D, int kMode, int kQueries>
+__device__ __forceinline__ void write_empty(const Item& it, const Out& out, int H, char* smem) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (32 * wave >= kQueries) return;
+  f32x16 zero[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db) zero[db] = f32x16{};
+  write_result<D, kMode>(it, out, zero, 0.0f, -INFINITY, H, it.q_begin + 32 * wave,
+                         (lds_char*)smem + Geo<D>::kOBase + wave * Geo<D>::kOWave, lane);
+}
+
 // kThin = false compiles the thin path out, for launches that have no query tile of at most
 // kThinQueries queries (the full tiles' code is then exactly that of a build without it).
 template <int D, int kMode, bool kThin = true>
@@ -1135,12 +1579,7 @@ __device__ __forceinline__ void run_item(const Item& it, const __bf16* __restric
                                          const Out& out, int H, float c, bool negate_q, char* smem) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (it.ntiles <= 0) {  // no keys in this item (the whole workgroup leaves together)
-    const int lane = threadIdx.x & 63;
-    f32x16 zero[D / 32];
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) zero[db] = f32x16{};
-    write_result<D, kMode>(it, out, zero, 0.0f, -INFINITY, H, it.q_begin + 32 * wave,
-                           (lds_char*)smem + Geo<D>::kOBase + wave * Geo<D>::kOWave, lane);
+    write_empty<D, kMode, kBM>(it, out, H, smem);
     return;
   }
   if (kThin && it.q_len - it.q_begin <= kThinQueries) {
@@ -1187,35 +1626,124 @@ attn_dense_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   run_item<D, kFinal, kThin>(it, q, k, v, out, H, c, negate_q != 0, smem);
 }
 
+// A 64-query item.  Query tiles that the 256-query kernel runs as thin items are run as such here too,
+// so that a row's result does not depend on the item size.
+template <int D, int kMode>
+__device__ __forceinline__ void run_small_or_thin(const Item& it, const __bf16* __restrict__ q,
+                                                  const __bf16* __restrict__ k,
+                                                  const __bf16* __restrict__ v, const Out& out, int H,
+                                                  float c, bool negate_q, char* smem) {
+  if (it.ntiles <= 0)
+    write_empty<D, kMode, kSmallTile>(it, out, H, smem);
+  else if (it.q_begin % kBM == 0 && it.q_len - it.q_begin <= kThinQueries)
+    run_thin_item<D, kMode>(it, q, k, v, out, H, c, negate_q, smem);
+  else
+    run_small_item<D, kMode>(it, q, k, v, out, H, c, negate_q, smem);
+}
+
+// The dense call in 64-query items, head-major.
+template <int D>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+attn_dense_small_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
+                        const __bf16* __restrict__ v, __bf16* __restrict__ o, int L, int H, int nq,
+                        int total, int chunk, float c, int negate_q) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int item = remap_block(blockIdx.x, total, chunk);
+  const int bh = item / nq, qt = item % nq;
+  Item it;
+  it.q_start = it.k_start = (int64_t)(bh / H) * L;
+  it.q_len = it.k_len = L;
+  it.h = bh % H;
+  it.q_begin = qt * kSmallTile;
+  it.tile_begin = 0;
+  it.ntiles = (L + Geo<D>::kBN - 1) / Geo<D>::kBN;
+  Out out{o, nullptr, nullptr, nullptr, 0, 0};
+  run_small_or_thin<D, kFinal>(it, q, k, v, out, H, c, negate_q != 0, smem);
+}
+
 // Packed batch: segment s has queries [cu_q[s], cu_q[s+1]) and keys [cu_k[s], cu_k[s+1])
 // (cu_k == cu_q for self-attention).  Each (segment, head, query tile) is split into n_split
 // items over consecutive ranges of the segment's key tiles (n_split = 1: one item, kFinal).
 // plan layout (int32): [0] item count, [1] error flag, then per rank r (most keys first):
 // [2 + 2r] segment index, [3 + 2r] first item of that segment.  The items of a segment are
 // ordered head-major, then split, then query tile, so consecutive items share K/V ranges.
-// plan = null: a batch of one segment, run without a planning kernel.  Its only valid offsets
-// are {0, total_q} and {0, total_k}; every workgroup checks them and the call is a no-op
-// otherwise, as with a rejected plan.
-__device__ __forceinline__ bool one_segment_valid(const int32_t* __restrict__ cu_q,
-                                                  const int32_t* __restrict__ cu_k, int total_q,
-                                                  int total_k) {
-  return cu_q[0] == 0 && cu_q[1] == total_q && cu_k[0] == 0 && cu_k[1] == total_k;
+// plan = null: a batch of at most kWavePlanSegs segments, run without a planning kernel: every wave
+// checks the offsets and finds its item's segment itself (WavePlan).
+
+// The plan of a batch of at most 64 segments, made by one wave in registers: lane s holds segment s.
+// Same rules and item order as plan_kernel's.  The offsets come in one memory latency, as long as
+// reading a plan would take; a plan kernel before the attention kernel costs 4 to 8 us.
+struct WavePlan {
+  int q0, q1, k0, k1;  // the lane's segment (zeros in the lanes past the last one)
+  bool valid;          // of the whole batch
+
+  __device__ __forceinline__ WavePlan(const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
+                                      int nseq, const PackedSizes& n, int lane) {
+    bool bad = false;
+    q0 = q1 = k0 = k1 = 0;
+    if (lane < nseq) {
+      q0 = cu_q[lane], q1 = cu_q[lane + 1], k0 = cu_k[lane], k1 = cu_k[lane + 1];
+      // every offset within [0, total] before any difference is taken, as in plan_kernel
+      bad = q0 < 0 || q1 > n.total_q || q1 < q0 || q1 - q0 > n.max_q || k0 < 0 || k1 > n.total_k ||
+            k1 < k0 || k1 - k0 > n.max_k;
+      if (lane == 0 && (q0 != 0 || k0 != 0)) bad = true;
+      if (lane == nseq - 1 && (q1 != n.total_q || k1 != n.total_k)) bad = true;
+    }
+    valid = __builtin_amdgcn_ballot_w64(bad) == 0;
+  }
+
+  // Items of the lane's segment, and its first item: the segments lie in order of their keys, most
+  // first.  Returns the items of the batch.
+  __device__ __forceinline__ int order(int nseq, int per_tile, int bm, int lane, int* first) const {
+    const int len = k1 - k0, cnt = per_tile * ((q1 - q0 + bm - 1) / bm);
+    int f = 0, total = 0;
+    for (int j = 0; j < nseq; ++j) {
+      const int lj = __builtin_amdgcn_readlane(len, j), cj = __builtin_amdgcn_readlane(cnt, j);
+      f += lj > len || (lj == len && j < lane) ? cj : 0;
+      total += cj;
+    }
+    *first = f;
+    return total;
+  }
+};
+
+// n / d for 0 <= n < 2^23 and 1 <= d < 2^23 (float division is off by one at most there)
+__device__ __forceinline__ int small_div(int n, int d) {
+  int q = (int)((float)n * __builtin_amdgcn_rcpf((float)d));
+  const int r = n - q * d;
+  if (r < 0) --q;
+  if (r >= d) ++q;
+  return q;
 }
 
-template <int D, int kMode>
+// kSmall: 64-query items (run_small_item).
+template <int D, int kMode, bool kSmall>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attn_varlen_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                    const __bf16* __restrict__ v, Out out, const int32_t* __restrict__ cu_q,
                    const int32_t* __restrict__ cu_k, const int32_t* __restrict__ plan, int nseq,
-                   int H, int n_split, int chunk, float c, int negate_q, int total_q,
-                   int total_k) {
+                   PackedSizes sizes, int H, int n_split, int chunk, float c, int negate_q) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  int s = 0, local;
+  constexpr int kTile = kSmall ? kSmallTile : kBM;
+  int local;
+  Item it;
   if (plan == nullptr) {
-    if (!one_segment_valid(cu_q, cu_k, total_q, total_k)) return;
-    const int total = H * n_split * ((total_q + kBM - 1) / kBM);
+    const int lane = threadIdx.x & 63;
+    const WavePlan wp(cu_q, cu_k, nseq, sizes, lane);
+    if (!wp.valid) return;
+    int first;
+    const int total = wp.order(nseq, H * n_split, kTile, lane, &first);
     if ((int)blockIdx.x >= total) return;
-    local = remap_block(blockIdx.x, total, chunk);
+    const int item = remap_block(blockIdx.x, total, chunk);
+    // the segment that holds the item: the last in the order whose first item is <= item (empty
+    // segments share starts with the next one, and hold none)
+    const int cnt = H * n_split * ((wp.q1 - wp.q0 + kTile - 1) / kTile);
+    const int s = __builtin_ctzll(__builtin_amdgcn_ballot_w64(first <= item && item - first < cnt));
+    local = item - __builtin_amdgcn_readlane(first, s);
+    it.q_start = __builtin_amdgcn_readlane(wp.q0, s);
+    it.q_len = __builtin_amdgcn_readlane(wp.q1, s) - (int)it.q_start;
+    it.k_start = __builtin_amdgcn_readlane(wp.k0, s);
+    it.k_len = __builtin_amdgcn_readlane(wp.k1, s) - (int)it.k_start;
   } else {
     const int total = plan[0];
     if ((int)blockIdx.x >= total) return;
@@ -1226,25 +1754,26 @@ attn_varlen_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
       int mid = (lo + hi) >> 1;
       if (plan[3 + 2 * mid] <= item) lo = mid; else hi = mid;
     }
-    s = plan[2 + 2 * lo];
+    const int s = plan[2 + 2 * lo];
     local = item - plan[3 + 2 * lo];
+    it.q_start = cu_q[s];
+    it.q_len = cu_q[s + 1] - cu_q[s];
+    it.k_start = cu_k[s];
+    it.k_len = cu_k[s + 1] - cu_k[s];
   }
-  Item it;
-  it.q_start = cu_q[s];
-  it.q_len = cu_q[s + 1] - cu_q[s];
-  it.k_start = cu_k[s];
-  it.k_len = cu_k[s + 1] - cu_k[s];
-  const int nq = (it.q_len + kBM - 1) / kBM;
+  const int nq = (it.q_len + kTile - 1) / kTile;
   const int per_head = nq * n_split;
-  it.h = local / per_head;
-  const int split = (local % per_head) / nq;
-  it.q_begin = (local % nq) * kBM;
+  it.h = small_div(local, per_head);
+  local -= it.h * per_head;
+  const int split = n_split == 1 ? 0 : small_div(local, nq);
+  it.q_begin = (local - split * nq) * kTile;
   const int seg_tiles = (it.k_len + Geo<D>::kBN - 1) / Geo<D>::kBN;
-  const int per_split = (seg_tiles + n_split - 1) / n_split;
+  const int per_split = n_split == 1 ? seg_tiles : small_div(seg_tiles + n_split - 1, n_split);
   it.tile_begin = split * per_split;
   it.ntiles = max(0, min(per_split, seg_tiles - it.tile_begin));
   out.split = split;
-  run_item<D, kMode>(it, q, k, v, out, H, c, negate_q != 0, smem);
+  if constexpr (kSmall) run_small_or_thin<D, kMode>(it, q, k, v, out, H, c, negate_q != 0, smem);
+  else run_item<D, kMode>(it, q, k, v, out, H, c, negate_q != 0, smem);
 }
 
 // Combines the key ranges of a split call: for every (query row, head) with partial results
@@ -1256,14 +1785,14 @@ __global__ void __launch_bounds__(kMergeThreads)
 attn_merge_kernel(const float* __restrict__ part_o, const float* __restrict__ part_lse,
                   int n_split, int64_t rows, __bf16* __restrict__ o, float* __restrict__ lse,
                   const int32_t* __restrict__ plan, const int32_t* __restrict__ cu_q,
-                  const int32_t* __restrict__ cu_k, int total_q, int total_k) {
+                  const int32_t* __restrict__ cu_k, int nseq, PackedSizes sizes) {
   constexpr int kChunks = D / 8;
   const int64_t gid = (int64_t)blockIdx.x * kMergeThreads + threadIdx.x;
   const int64_t row = gid / kChunks;
   const int c8 = (int)(gid % kChunks);
   // rejected offsets wrote no partials: O stays as is
+  if (plan != nullptr ? plan[1] != 0 : !WavePlan(cu_q, cu_k, nseq, sizes, threadIdx.x & 63).valid) return;
   if (row >= rows) return;
-  if (plan != nullptr ? plan[1] != 0 : !one_segment_valid(cu_q, cu_k, total_q, total_k)) return;
   float m = -INFINITY;
   for (int i = 0; i < n_split; ++i) m = fmaxf(m, part_lse[i * rows + row]);
   f32x4 a0 = {0.0f, 0.0f, 0.0f, 0.0f}, a1 = a0;
@@ -1292,7 +1821,7 @@ constexpr int kPlanSortMax = 4096;  // larger batches keep their given order
 
 __global__ void __launch_bounds__(kPlanThreads)
 plan_kernel(const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, int nseq,
-            int max_q, int max_k, int total_q, int total_k, int H, int n_split,
+            int max_q, int max_k, int total_q, int total_k, int H, int n_split, int bm,
             int32_t* __restrict__ plan) {
   __shared__ uint64_t keys[kPlanSortMax];
   __shared__ int32_t scan[kPlanThreads];
@@ -1339,7 +1868,7 @@ plan_kernel(const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, 
         __syncthreads();
       }
   }
-  // exclusive prefix sum of H * n_split * ceil(queries / kBM) in rank order, 1024 ranks per pass
+  // exclusive prefix sum of H * n_split * ceil(queries / bm) in rank order, 1024 ranks per pass
   int carry = 0;
   for (int base = 0; base < nseq; base += kPlanThreads) {
     int r = base + tid;
@@ -1347,7 +1876,7 @@ plan_kernel(const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, 
     if (r < nseq) {
       seg = sorted ? (int)(keys[r] & 0xffffffffu) : r;
       const int lq = cu_q[seg + 1] - cu_q[seg];
-      cnt = H * n_split * ((lq + kBM - 1) / kBM);
+      cnt = H * n_split * ((lq + bm - 1) / bm);
     }
     scan[tid] = cnt;
     __syncthreads();
@@ -1383,6 +1912,13 @@ static hipError_t launch_dense_d(const DenseArgs& a, hipStream_t st) {
   const int nq = (a.L + kBM - 1) / kBM;
   const int total = a.B * a.H * nq;
   const float c = softmax_factor(a.scale);
+  if (a.small) {
+    const int n = (a.L + kSmallTile - 1) / kSmallTile, total_small = a.B * a.H * n;
+    hipLaunchKernelGGL(attn_dense_small_kernel<D>, dim3(total_small), dim3(kThreads), SmallGeo<D>::kLds,
+                       st, (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v, (__bf16*)a.o,
+                       a.L, a.H, n, total_small, a.xcd_chunk, c, a.scale < 0.0f ? 1 : 0);
+    return hipGetLastError();
+  }
   const int tail = a.L % kBM;
   auto kern = tail != 0 && tail <= kThinQueries ? attn_dense_kernel<D, true>
                                                 : attn_dense_kernel<D, false>;
@@ -1395,59 +1931,59 @@ static hipError_t launch_dense_d(const DenseArgs& a, hipStream_t st) {
 template <int D>
 static hipError_t launch_packed_d(const PackedArgs& a, hipStream_t st) {
   hipError_t e;
+  const int tile = a.small ? kSmallTile : kBM;
   if (a.plan != nullptr) {
     hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, a.cu_q, a.cu_k, a.nseq,
-                       a.max_q, a.max_k, a.total_q, a.total_k, a.H, a.n_split, a.plan);
+                       a.max_q, a.max_k, a.total_q, a.total_k, a.H, a.n_split, tile, a.plan);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  const int64_t grid = packed_grid_bound(a.total_q, a.nseq, a.H, a.n_split);
+  const int64_t grid = packed_items(a.total_q, a.nseq, a.H, a.n_split, tile);
   const float c = softmax_factor(a.scale);
   const int neg = a.scale < 0.0f ? 1 : 0;
   Out out{(__bf16*)a.o, a.lse, a.part_o, a.part_lse, a.total_q, 0};
-  if (a.n_split == 1) {
-    hipLaunchKernelGGL((attn_varlen_kernel<D, kFinal>), dim3((unsigned)grid), dim3(kThreads),
-                       Geo<D>::kLds, st, (const __bf16*)a.q, (const __bf16*)a.k,
-                       (const __bf16*)a.v, out, a.cu_q, a.cu_k, a.plan, a.nseq, a.H, 1,
-                       a.xcd_chunk, c, neg, a.total_q, a.total_k);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL((attn_varlen_kernel<D, kPartial>), dim3((unsigned)grid), dim3(kThreads),
-                     Geo<D>::kLds, st, (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v,
-                     out, a.cu_q, a.cu_k, a.plan, a.nseq, a.H, a.n_split, a.xcd_chunk, c, neg,
-                     a.total_q, a.total_k);
+  const PackedSizes sizes{a.max_q, a.max_k, a.total_q, a.total_k};
+  auto kern = a.n_split == 1 ? (a.small ? attn_varlen_kernel<D, kFinal, true> : attn_varlen_kernel<D, kFinal, false>)
+                             : (a.small ? attn_varlen_kernel<D, kPartial, true> : attn_varlen_kernel<D, kPartial, false>);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads),
+                     a.small ? SmallGeo<D>::kLds : Geo<D>::kLds, st, (const __bf16*)a.q,
+                     (const __bf16*)a.k, (const __bf16*)a.v, out, a.cu_q, a.cu_k, a.plan, a.nseq, sizes,
+                     a.H, a.n_split, a.xcd_chunk, c, neg);
   e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || a.n_split == 1) return e;
   const int64_t rows = (int64_t)a.total_q * a.H;
   const int64_t threads = rows * (D / 8);
   const int64_t blocks = (threads + kMergeThreads - 1) / kMergeThreads;
   hipLaunchKernelGGL((attn_merge_kernel<D>), dim3((unsigned)blocks), dim3(kMergeThreads), 0, st,
                      a.part_o, a.part_lse, a.n_split, rows, (__bf16*)a.o, a.lse, a.plan, a.cu_q,
-                     a.cu_k, a.total_q, a.total_k);
+                     a.cu_k, a.nseq, sizes);
   return hipGetLastError();
 }
 
-hipError_t configure_kernels() {
-  hipError_t e;
-  const void* dense[4] = {(const void*)attn_dense_kernel<64, false>,
-                          (const void*)attn_dense_kernel<64, true>,
-                          (const void*)attn_dense_kernel<128, false>,
-                          (const void*)attn_dense_kernel<128, true>};
-  for (int i = 0; i < 4; ++i) {
-    e = hipFuncSetAttribute(dense[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                            i < 2 ? Geo<64>::kLds : Geo<128>::kLds);
-    if (e != hipSuccess) return e;
-  }
-  const void* packed[4] = {(const void*)attn_varlen_kernel<64, kFinal>,
-                           (const void*)attn_varlen_kernel<64, kPartial>,
-                           (const void*)attn_varlen_kernel<128, kFinal>,
-                           (const void*)attn_varlen_kernel<128, kPartial>};
-  for (int i = 0; i < 4; ++i) {
-    e = hipFuncSetAttribute(packed[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                            i < 2 ? Geo<64>::kLds : Geo<128>::kLds);
+// Every kernel takes more dynamic LDS than the runtime allows by default.
+template <int D>
+static hipError_t configure_d() {
+  const struct {
+    const void* kern;
+    int lds;
+  } all[] = {{(const void*)attn_dense_kernel<D, false>, Geo<D>::kLds},
+             {(const void*)attn_dense_kernel<D, true>, Geo<D>::kLds},
+             {(const void*)attn_dense_small_kernel<D>, SmallGeo<D>::kLds},
+             {(const void*)attn_varlen_kernel<D, kFinal, false>, Geo<D>::kLds},
+             {(const void*)attn_varlen_kernel<D, kFinal, true>, SmallGeo<D>::kLds},
+             {(const void*)attn_varlen_kernel<D, kPartial, false>, Geo<D>::kLds},
+             {(const void*)attn_varlen_kernel<D, kPartial, true>, SmallGeo<D>::kLds}};
+  for (const auto& k : all) {
+    const hipError_t e =
+        hipFuncSetAttribute(k.kern, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t configure_kernels() {
+  const hipError_t e = configure_d<64>();
+  return e != hipSuccess ? e : configure_d<128>();
 }
 
 // Scratch of the allocation-free chunk call: its plan and, for split calls, the float32 partial

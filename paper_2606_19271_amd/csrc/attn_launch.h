@@ -14,6 +14,7 @@ struct DenseArgs {
   int32_t B, L, H, d;
   float scale;
   int xcd_chunk;  // consecutive items per XCD (CUs per XCD x workgroups per CU)
+  bool small;     // 64-query items (small_items)
 };
 
 // A packed batch: segment s has queries [cu_q[s], cu_q[s+1]) of q/o and keys/values
@@ -31,14 +32,17 @@ struct PackedArgs {
   int32_t nseq, max_q, max_k, total_q, total_k, H, d, n_split;
   float scale;
   int xcd_chunk;
-  int32_t* plan;         // device, plan_ints(nseq) entries; null for a batch of one segment
-                         // run without the planning kernel
+  int32_t* plan;         // device, plan_ints(nseq) entries; null for a batch of at most
+                         // kWavePlanSegs segments run without the planning kernel
   float* part_o;         // device [n_split][total_q][H][d] (n_split > 1)
   float* part_lse;       // device [n_split][total_q][H] (n_split > 1)
+  bool small;            // 64-query items (small_items)
 };
 
 // Sizes shared by the kernels and the host-side planning (attn_plan.cpp).
 constexpr int kQueryTile = 256;             // queries per work item of the attention kernels
+constexpr int kSmallTile = 64;              // and of their variants for small grids
+constexpr int kWavePlanSegs = 64;           // segments that a wave plans by itself, one per lane
 constexpr int kMergeThreads = 256;          // threads per workgroup of the merge kernel
 // Keys per K/V tile of the attention kernels at head width d (64 or 128).
 constexpr int key_tile(int d) { return d == 64 ? 128 : 64; }
@@ -47,8 +51,13 @@ constexpr int64_t kCopyChunkBytes = 32768;  // bytes copied by one state-copy wo
 // partials), one per device, held from the library's load until the process ends.
 constexpr int64_t kScratchBytes = (int64_t)32 << 20;
 
-// Upper bound of the number of work items of a packed batch (its launch grid).
+// Upper bound of the number of work items of a packed batch that the size limits are stated in.
 int64_t packed_grid_bound(int32_t total_q, int32_t nseq, int32_t H, int32_t n_split);
+// Tight upper bound of the number of work items of `tile` queries of a packed batch (its launch grid).
+int64_t packed_items(int32_t total_q, int32_t nseq, int32_t H, int32_t n_split, int32_t tile);
+// Whether a call of at most `items` 64-query work items, over at most max_k keys each, runs in those
+// instead of 256-query ones.
+bool small_items(int64_t items, int32_t max_k, int32_t cus);
 // Workgroups of the merge kernel of a split call.
 int64_t merge_blocks(int32_t total_q, int32_t H, int32_t d);
 // int32 entries of the plan buffer for nseq segments.

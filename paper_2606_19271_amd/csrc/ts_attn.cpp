@@ -229,19 +229,28 @@ void carve(tsattn::PackedArgs& a, char* buf) {
   }
 }
 
-// A batch of one segment runs without the planning kernel: its only valid offsets are {0, total_q}
-// and {0, total_k}, which the attention and merge kernels check themselves (a mismatch makes the
-// call a device-side no-op, as a rejected plan does).  Totals beyond the stated maximum lengths
-// admit no valid offsets at all, so such a call is a no-op without any device work.
-bool one_segment_possible(const tsattn::PackedArgs& a) {
-  return a.total_q <= a.max_q && a.total_k <= a.max_k;
+// A batch of at most kWavePlanSegs segments runs without the planning kernel: the attention and merge
+// kernels check its offsets themselves (a mismatch makes the call a device-side no-op, as a rejected
+// plan does).
+bool planless(const tsattn::PackedArgs& a) { return a.nseq <= tsattn::kWavePlanSegs; }
+
+// With one segment, totals beyond the stated maximum lengths admit no valid offsets at all: such a
+// call is a no-op without any device work.
+bool no_valid_offsets(const tsattn::PackedArgs& a) {
+  return a.nseq == 1 && (a.total_q > a.max_q || a.total_k > a.max_k);
+}
+
+// Whether the call's query tiles are 64 queries (a.n_split is set).
+bool small_tiles(const tsattn::PackedArgs& a, int32_t cus) {
+  return tsattn::small_items(
+      tsattn::packed_items(a.total_q, a.nseq, a.H, a.n_split, tsattn::kSmallTile), a.max_k, cus);
 }
 
 // Launch of a packed call whose plan (and partials) sit in buf, and the validation-mode read-back
 // of the plan's error flag (a host synchronization, in validation mode only).
-int launch_with(tsattn::PackedArgs a, char* buf, bool single, bool validate, hipStream_t s) {
+int launch_with(tsattn::PackedArgs a, char* buf, bool without_plan, bool validate, hipStream_t s) {
   carve(a, buf);
-  if (single) a.plan = nullptr;  // a split call of one segment: partials only
+  if (without_plan) a.plan = nullptr;  // partials only
   int rc = tsattn::launch_packed(a, s) == hipSuccess ? TS_OK : TS_ERR_HIP;
   if (rc == TS_OK && validate) {
     int32_t head[2] = {0, 0};
@@ -261,9 +270,10 @@ constexpr size_t kWorkspaceCache = (size_t)256 << 20;
 int run_packed(DeviceState* st, tsattn::PackedArgs a, hipStream_t s) {
   const bool validate = validate_mode();
   // validation mode keeps the plan, whose error flag it reads back
-  const bool single = a.nseq == 1 && !validate;
-  if (single) {
-    if (!one_segment_possible(a)) return TS_OK;
+  const bool without_plan = planless(a) && !validate;
+  a.small = small_tiles(a, st->cus);
+  if (without_plan) {
+    if (no_valid_offsets(a)) return TS_OK;
     if (a.n_split == 1) {  // no device memory at all
       a.plan = nullptr;
       return tsattn::launch_packed(a, s) == hipSuccess ? TS_OK : TS_ERR_HIP;
@@ -297,7 +307,7 @@ int run_packed(DeviceState* st, tsattn::PackedArgs a, hipStream_t s) {
       }
       st->ws_size = want;
     }
-    int rc = launch_with(a, (char*)st->ws, single, validate, s);
+    int rc = launch_with(a, (char*)st->ws, without_plan, validate, s);
     if (hipEventRecord(st->ws_done, s) != hipSuccess && rc == TS_OK) rc = TS_ERR_HIP;
     st->ws_used = true;
     return rc;
@@ -306,7 +316,7 @@ int run_packed(DeviceState* st, tsattn::PackedArgs a, hipStream_t s) {
   if (!pool) return TS_ERR_NOMEM;
   char* buf = nullptr;
   if (hipMallocFromPoolAsync((void**)&buf, bytes, pool, s) != hipSuccess) return TS_ERR_NOMEM;
-  int rc = launch_with(a, buf, single, validate, s);
+  int rc = launch_with(a, buf, without_plan, validate, s);
   if (hipFreeAsync(buf, s) != hipSuccess && rc == TS_OK) rc = TS_ERR_HIP;
   return rc;
 }
@@ -362,9 +372,10 @@ int run_static(DeviceState* st, tsattn::PackedArgs a, int32_t n, hipStream_t s) 
     return TS_ERR_SCRATCH;
   }
   a.n_split = n;
+  a.small = small_tiles(a, st->cus);
   carve(a, (char*)st->scratch);
-  if (a.nseq == 1) {
-    if (!one_segment_possible(a)) return TS_OK;
+  if (planless(a)) {
+    if (no_valid_offsets(a)) return TS_OK;
     a.plan = nullptr;
   }
   return tsattn::launch_packed(a, s) == hipSuccess ? TS_OK : TS_ERR_HIP;
@@ -405,7 +416,9 @@ int ts_attn_fwd(const void* q, const void* k, const void* v, void* o, int32_t B,
   if (B == 0 || L == 0) return TS_OK;
   DeviceState* st = current_device(&rc, (hipStream_t)stream);
   if (!st) return rc;
-  tsattn::DenseArgs a{q, k, v, o, B, L, H, d, scale, st->xcd_chunk};
+  const int64_t small = (int64_t)B * H * ((L + tsattn::kSmallTile - 1) / tsattn::kSmallTile);
+  tsattn::DenseArgs a{q, k, v, o, B, L, H, d, scale, st->xcd_chunk,
+                      tsattn::small_items(small, L, st->cus)};
   return tsattn::launch_dense(a, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 
@@ -422,7 +435,7 @@ int ts_attn_fwd_varlen(const void* q, const void* k, const void* v, void* o,
   if (!st) return rc;
   tsattn::PackedArgs a{q, k, v, o, nullptr, cu_seqlens, cu_seqlens, nseq, max_seqlen, max_seqlen,
                        total_tokens, total_tokens, H, d, 1, scale, st->xcd_chunk,
-                       nullptr, nullptr, nullptr};
+                       nullptr, nullptr, nullptr, false};
   if (capturing((hipStream_t)stream)) return run_static(st, a, 1, (hipStream_t)stream);
   return run_packed(st, a, (hipStream_t)stream);
 }
@@ -440,7 +453,7 @@ int ts_attn_fwd_kvcache(const void* q, const void* k, const void* v, void* o, fl
   if (!st) return rc;
   tsattn::PackedArgs a{q, k, v, o, lse, cu_seqlens_q, cu_seqlens_k, nseq, max_seqlen_q,
                        max_seqlen_k, total_q, total_k, H, d, 1, scale, st->xcd_chunk,
-                       nullptr, nullptr, nullptr};
+                       nullptr, nullptr, nullptr, false};
   if (capturing((hipStream_t)stream)) return run_static(st, a, num_splits, (hipStream_t)stream);
   a.n_split = num_splits > 0 ? num_splits : auto_splits(st->cus, total_q, max_seqlen_k, H, d);
   return run_packed(st, a, (hipStream_t)stream);
@@ -462,7 +475,7 @@ int ts_attn_fwd_kvcache_noalloc(const void* q, const void* k, const void* v, voi
   if (!st) return rc;
   tsattn::PackedArgs a{q, k, v, o, lse, cu_seqlens_q, cu_seqlens_k, nseq, max_seqlen_q,
                        max_seqlen_k, total_q, total_k, H, d, 1, scale, st->xcd_chunk,
-                       nullptr, nullptr, nullptr};
+                       nullptr, nullptr, nullptr, false};
   return run_static(st, a, num_splits, (hipStream_t)stream);
 }
 
