@@ -168,8 +168,8 @@ int ts_attn_fwd_kvcache(const void* q, const void* k, const void* v, void* o, fl
  *    ends), not in a per-call allocation.  A call needs
  *      align256(4 * (2 nseq + 2)) + [n > 1] (align256(4 n total_q H) + 4 n total_q H d)
  *    bytes for n key ranges.  A forced num_splits whose partials do not fit returns
- *    TS_ERR_SCRATCH before any HIP call; num_splits = 0 takes the library's choice, lowered to
- *    the largest n that fits (n = 1 always fits).
+ *    TS_ERR_SCRATCH before any HIP call; num_splits = 0 takes the library's choice among the n
+ *    that fit (n = 1 always fits).
  *  - Races: every call on a device shares that device's array, and a call leaves its contents
  *    behind.  Calls on one stream are ordered; calls that may overlap on one device (different
  *    streams, or host threads without ordering between their streams) race on the array and give

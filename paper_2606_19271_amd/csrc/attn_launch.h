@@ -58,6 +58,12 @@ int64_t packed_items(int32_t total_q, int32_t nseq, int32_t H, int32_t n_split, 
 // Whether a call of at most `items` 64-query work items, over at most max_k keys each, runs in those
 // instead of 256-query ones.
 bool small_items(int64_t items, int32_t max_k, int32_t cus);
+// What the host knows of a chunk call's lengths (nseq >= 1).
+struct SplitShape {
+  int32_t nseq, total_q, total_k, max_k, H, d;
+};
+// Key ranges per query tile, 1 .. max_n, when the caller leaves the choice to the library.
+int32_t auto_splits(const SplitShape& c, int32_t max_n, int32_t cus);
 // Workgroups of the merge kernel of a split call.
 int64_t merge_blocks(int32_t total_q, int32_t H, int32_t d);
 // int32 entries of the plan buffer for nseq segments.

@@ -184,27 +184,11 @@ int check_kv(const void* q, const void* k, const void* v, const void* o, const f
   return TS_OK;
 }
 
-// Key ranges per query tile when the caller leaves the choice to the library.  One 512-thread
-// workgroup runs per CU, so `items` work items take ceil(items / cus) rounds, each as long as
-// one item's key tiles.  Query tiles that already fill the GPU are not split (the partials would
-// only add traffic); otherwise n minimises rounds(items * n) * ceil(tiles / n), the smallest n
-// winning ties, with at least 4 key tiles per range.
-int32_t auto_splits(int cus, int32_t total_q, int32_t max_k, int32_t H, int32_t d) {
-  const int64_t items = (int64_t)H * ((total_q + tsattn::kQueryTile - 1) / tsattn::kQueryTile);
-  const int64_t kt = tsattn::key_tile(d);
-  const int64_t tiles = ((int64_t)max_k + kt - 1) / kt;
-  if (items <= 0 || items >= cus || tiles < 8) return 1;
-  int32_t best = 1;
-  int64_t best_cost = INT64_MAX;
-  for (int32_t n = 1; n <= kMaxSplits && tiles / n >= 4; ++n) {
-    const int64_t rounds = (items * n + cus - 1) / cus;
-    const int64_t cost = rounds * ((tiles + n - 1) / n);
-    if (cost < best_cost) { best_cost = cost; best = n; }
-  }
-  return best;
-}
-
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Workspaces up to this size come from the device's cached workspace; larger ones (long split
+// calls) from a stream-ordered pool allocation of their own.
+constexpr size_t kWorkspaceCache = (size_t)256 << 20;
 
 // Bytes of device scratch a packed call needs: the plan and, with n > 1 key ranges, the float32
 // partial lse [n][tq][H] and O [n][tq][H][d], each part 256-byte aligned.
@@ -215,6 +199,14 @@ int64_t scratch_bytes(int32_t nseq, int32_t n, int32_t tq, int32_t H, int32_t d)
     b += (int64_t)n * tq * H * d * (int64_t)sizeof(float);
   }
   return b;
+}
+
+// The library's choice of key ranges for a call whose scratch must not exceed `limit` bytes (one range
+// is always allowed).
+int32_t choose_splits(const tsattn::PackedArgs& a, int64_t limit, int32_t cus) {
+  int32_t max_n = kMaxSplits;
+  while (max_n > 1 && scratch_bytes(a.nseq, max_n, a.total_q, a.H, a.d) > limit) --max_n;
+  return tsattn::auto_splits({a.nseq, a.total_q, a.total_k, a.max_k, a.H, a.d}, max_n, cus);
 }
 
 // Points a.plan (and, for a split call, a.part_lse / a.part_o) into buf, laid out as in
@@ -262,10 +254,6 @@ int launch_with(tsattn::PackedArgs a, char* buf, bool without_plan, bool validat
   }
   return rc;
 }
-
-// Workspaces up to this size come from the device's cached workspace; larger ones (long split
-// calls) from a stream-ordered pool allocation of their own.
-constexpr size_t kWorkspaceCache = (size_t)256 << 20;
 
 int run_packed(DeviceState* st, tsattn::PackedArgs a, hipStream_t s) {
   const bool validate = validate_mode();
@@ -361,13 +349,12 @@ int copy_operand(const void* p, int dev, const void** devp, bool* host) {
 
 // A packed or chunk call on the device's static scratch array: the allocation-free entry point,
 // and the allocating ones on a capturing stream (where the workspace's event waits and growth, or
-// a pool allocation, have no place).  n = 0 takes the library's choice, lowered until its partial
+// a pool allocation, have no place).  n = 0 takes the library's choice among the n whose partial
 // results fit the scratch; a forced n that does not fit returns TS_ERR_SCRATCH.  Validation mode
 // does not apply: invalid offsets make the call a device-side no-op.
 int run_static(DeviceState* st, tsattn::PackedArgs a, int32_t n, hipStream_t s) {
   if (n == 0) {
-    n = auto_splits(st->cus, a.total_q, a.max_k, a.H, a.d);
-    while (n > 1 && scratch_bytes(a.nseq, n, a.total_q, a.H, a.d) > tsattn::kScratchBytes) --n;
+    n = choose_splits(a, tsattn::kScratchBytes, st->cus);
   } else if (scratch_bytes(a.nseq, n, a.total_q, a.H, a.d) > tsattn::kScratchBytes) {
     return TS_ERR_SCRATCH;
   }
@@ -455,7 +442,8 @@ int ts_attn_fwd_kvcache(const void* q, const void* k, const void* v, void* o, fl
                        max_seqlen_k, total_q, total_k, H, d, 1, scale, st->xcd_chunk,
                        nullptr, nullptr, nullptr, false};
   if (capturing((hipStream_t)stream)) return run_static(st, a, num_splits, (hipStream_t)stream);
-  a.n_split = num_splits > 0 ? num_splits : auto_splits(st->cus, total_q, max_seqlen_k, H, d);
+  // (within the cached workspace: beyond it the pool makes the host wait)
+  a.n_split = num_splits > 0 ? num_splits : choose_splits(a, kWorkspaceCache, st->cus);
   return run_packed(st, a, (hipStream_t)stream);
 }
 

@@ -1,0 +1,67 @@
+"""The library's choice of key ranges and item size for chunk calls (csrc/attn_plan.cpp, host code),
+compiled with g++ under ASan and UBSan with a driver that walks random and extreme shapes."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2606_19271_amd", "csrc")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+DRIVER = r"""
+#include <stdint.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include "attn_launch.h"
+using namespace tsattn;
+static int bad = 0;
+#define CHECK(x) do { if (!(x)) { printf("line %d: %s\n", __LINE__, #x); ++bad; } } while (0)
+int main() {
+  uint64_t r = 12345;
+  auto rnd = [&](int64_t n) { r = r * 6364136223846793005ull + 1442695040888963407ull; return (int64_t)(r >> 33) % n; };
+  const int32_t big[] = {0, 1, 63, 64, 65, 255, 256, 257, 32760, 8388607};
+  for (int i = 0; i < 200000; ++i) {
+    SplitShape c;
+    c.nseq = 1 + (int32_t)(rnd(3) ? rnd(70) : rnd(100000));
+    c.total_q = rnd(4) ? (int32_t)rnd(200000) : big[rnd(10)];
+    c.total_k = rnd(4) ? (int32_t)rnd(2000000) : big[rnd(10)];
+    c.max_k = rnd(4) ? (int32_t)rnd(100000) : big[rnd(10)];
+    c.H = 1 + (int32_t)rnd(128);
+    c.d = rnd(2) ? 64 : 128;
+    const int32_t max_n = 1 + (int32_t)rnd(16);
+    const int32_t n = auto_splits(c, max_n, 256);
+    const int64_t tiles = ((int64_t)c.max_k + key_tile(c.d) - 1) / key_tile(c.d);
+    CHECK(n >= 1 && n <= max_n && (n == 1 || tiles / n >= 4));
+    // the launch grid holds every item, whatever the lengths: equal ones, and all but one empty
+    const int32_t tile = rnd(2) ? kSmallTile : kQueryTile;
+    const int64_t per = (int64_t)c.H * n, t = tile;
+    const int64_t even = c.total_q / c.nseq, more = c.total_q % c.nseq;
+    const int64_t items = per * ((c.nseq - more) * ((even + t - 1) / t) + more * ((even + t) / t));
+    CHECK(packed_items(c.total_q, c.nseq, c.H, n, tile) >= items);
+    CHECK(packed_items(c.total_q, c.nseq, c.H, n, tile) >= per * ((c.total_q + t - 1) / t));
+    CHECK(packed_items(c.total_q, c.nseq, c.H, n, kQueryTile) <= packed_grid_bound(c.total_q, c.nseq, c.H, n));
+  }
+  // a call that fills the GPU for many rounds is not split; one 24-item call over 512 tiles is
+  CHECK(auto_splits({1, 32760, 32760, 32760, 40, 128}, 16, 256) == 1);
+  CHECK(auto_splits({1, 500, 32760, 32760, 12, 128}, 16, 256) > 4);
+  CHECK(!small_items(257, 4096, 256) && small_items(256, 4096, 256) && !small_items(1, 64, 256));
+  printf("failures %d\n", bad);
+  return bad != 0;
+}
+"""
+
+
+def test_split_choice(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    src, exe = tmp_path / "driver.cpp", str(tmp_path / "driver")
+    src.write_text(DRIVER)
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
+                        "-fno-sanitize-recover=all", "-Wall", "-Wextra", "-Werror", "-D__HIP_PLATFORM_AMD__",
+                        "-I" + os.path.join(ROCM, "include"), "-I" + CSRC, str(src),
+                        os.path.join(CSRC, "attn_plan.cpp"), "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "failures 0" in r.stdout, r.stdout + r.stderr
