@@ -46,7 +46,8 @@ constexpr int kWavePlanSegs = 64;           // segments that a wave plans by its
 constexpr int kMergeThreads = 256;          // threads per workgroup of the merge kernel
 // Keys per K/V tile of the attention kernels at head width d (64 or 128).
 constexpr int key_tile(int d) { return d == 64 ? 128 : 64; }
-constexpr int64_t kCopyChunkBytes = 32768;  // bytes copied by one state-copy workgroup
+constexpr int64_t kCopyChunkBytes = 16384;      // bytes of a state-copy workgroup's chunk
+constexpr int64_t kHostReadChunkBytes = 32768;  // and where the source is host memory
 // Bytes of the static device scratch array of the allocation-free chunk call (plan and split
 // partials), one per device, held from the library's load until the process ends.
 constexpr int64_t kScratchBytes = (int64_t)32 << 20;
@@ -71,7 +72,7 @@ int64_t plan_ints(int32_t nseq);
 
 // Up to kMaxCopyRanges byte-range copies of one state-copy launch (passed by value as a kernel
 // argument): range r copies bytes[r] bytes from src + src[r] to dst + dst[r]; first_chunk is the
-// prefix over the ranges of ceil(bytes / copy_chunk_bytes()), first_chunk[n] = chunks in all.
+// prefix over the ranges of ceil(bytes / copy_chunk_bytes(src_host)), first_chunk[n] = chunks in all.
 constexpr int kMaxCopyRanges = 64;
 struct CopyList {
   int64_t src[kMaxCopyRanges];
@@ -80,8 +81,8 @@ struct CopyList {
   int64_t first_chunk[kMaxCopyRanges + 1];
   int32_t n;
 };
-int64_t copy_chunk_bytes();
-// src_host / dst_host: that side is pinned host memory (accessed non-temporally).
+int64_t copy_chunk_bytes(bool src_host);
+// src_host / dst_host: that side is pinned host memory.
 hipError_t launch_state_copy(const void* src, void* dst, const CopyList& list, bool src_host,
                              bool dst_host, hipStream_t st);
 

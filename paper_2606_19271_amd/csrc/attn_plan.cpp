@@ -88,6 +88,6 @@ int64_t merge_blocks(int32_t total_q, int32_t H, int32_t d) {
 
 int64_t plan_ints(int32_t nseq) { return 2 + 2 * (int64_t)nseq; }
 
-int64_t copy_chunk_bytes() { return kCopyChunkBytes; }
+int64_t copy_chunk_bytes(bool src_host) { return src_host ? kHostReadChunkBytes : kCopyChunkBytes; }
 
 }  // namespace tsattn

@@ -7,13 +7,22 @@
 // one contiguous byte range, so suspend, resume and the compaction of a packed batch after
 // sessions leave are all lists of range copies: dst[d, d + n) = src[s, s + n).
 //
-// Design: one launch copies up to kMaxRanges ranges, passed by value in the kernel arguments
-// (no device allocation, no host-to-device upload).  Every range is cut into 32 KiB chunks; one
-// 256-thread workgroup copies one chunk with 16-byte accesses, eight loads in flight per thread
-// before the stores, so a host-memory side keeps many PCIe requests outstanding.  The chunk
-// index space is dense: a prefix over the ranges' chunk counts maps a workgroup to its range.
-// Pinned host memory is reached directly at its (unified) virtual address; the side that lives
-// in host memory uses non-temporal accesses, which bypass the GPU caches.
+// Design: one launch copies up to kMaxCopyRanges ranges, passed by value in the kernel arguments
+// (no device allocation, no host-to-device upload).  Every range is cut into chunks of one 256-thread
+// workgroup's 16-byte accesses, all loads of a chunk in flight before its stores.  The chunk index
+// space is dense: a prefix over the ranges' chunk counts maps a chunk to its range.  Pinned host
+// memory is reached directly at its (unified) virtual address.  What bounds each direction, measured
+// on 200 MB to 1.8 GB:
+//  * device -> device, HBM: chunks of 16 KiB, one per workgroup, non-temporal on both sides (the data
+//    is larger than the caches): 6.2 TB/s read + written.  Chunks of 32 KiB reach 4.2-4.4 TB/s with or
+//    without non-temporal accesses, 16 KiB with plain ones 5.7.  Copies of up to 32 MiB, which the
+//    caches hold for the next reader, keep plain accesses.
+//  * device -> host, the link's writes: 32 workgroups walk the chunks together, so that the link sees
+//    nearly consecutive writes: 55.6 GB/s, against 53.6 with a workgroup per chunk, whose order the
+//    dispatcher scatters (8 workgroups 51.4, 16 55.0, 24 55.7, 48 55.3, 256 52.4).  Each loads its
+//    next chunk before it stores the one before.
+//  * host -> device, the link's reads: many outstanding requests, 32 KiB a workgroup: 57.1 GB/s
+//    (16 KiB: 55.0; 16 or 32 workgroups in a walk: 57.0).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -22,41 +31,80 @@
 namespace tsstate {
 
 constexpr int kThreads = 256;
-constexpr int kPerThread = 8;                      // 16-byte vectors per thread per chunk
-constexpr int64_t kChunk = kThreads * kPerThread * 16;  // 32 KiB
-static_assert(kChunk == tsattn::kCopyChunkBytes, "chunk size shared with the host planning");
+constexpr int kWalkers = 32;  // workgroups of a device -> host copy
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-template <bool kNtLoad, bool kNtStore>
-__global__ void __launch_bounds__(kThreads)
-state_copy_kernel(const char* __restrict__ src, char* __restrict__ dst, tsattn::CopyList list) {
-  const int64_t c = blockIdx.x;
-  // the range holding chunk c: last r with first_chunk[r] <= c (empty ranges own no chunk)
-  int lo = 0, hi = list.n;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (list.first_chunk[mid] <= c) lo = mid; else hi = mid;
+// Chunk c of the copy: its vectors, of which the workgroup's thread t has t, t + 256, ...
+template <int kVectors>
+struct Chunk {
+  const u32x4* src;
+  u32x4* dst;
+  int nvec;
+
+  __device__ __forceinline__ Chunk(const char* s, char* d, const tsattn::CopyList& list, int64_t c) {
+    // the range holding chunk c: last r with first_chunk[r] <= c (empty ranges own no chunk)
+    int lo = 0, hi = list.n;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (list.first_chunk[mid] <= c) lo = mid; else hi = mid;
+    }
+    constexpr int64_t kBytes = (int64_t)kThreads * kVectors * 16;
+    const int64_t off = (c - list.first_chunk[lo]) * kBytes, left = list.bytes[lo] - off;
+    nvec = (int)((left < kBytes ? left : kBytes) >> 4);
+    src = (const u32x4*)(s + list.src[lo] + off);
+    dst = (u32x4*)(d + list.dst[lo] + off);
   }
-  const int64_t off = (c - list.first_chunk[lo]) * kChunk;
-  const int64_t left = list.bytes[lo] - off;
-  const int nvec = (int)((left < kChunk ? left : kChunk) >> 4);
-  const u32x4* s = (const u32x4*)(src + list.src[lo] + off);
-  u32x4* d = (u32x4*)(dst + list.dst[lo] + off);
-  u32x4 r[kPerThread];
+  template <bool kNt>
+  __device__ __forceinline__ void load(u32x4 (&r)[kVectors]) const {
 #pragma unroll
-  for (int u = 0; u < kPerThread; ++u) {
-    const int i = threadIdx.x + u * kThreads;
-    if (i < nvec) r[u] = kNtLoad ? __builtin_nontemporal_load(&s[i]) : s[i];
-  }
-#pragma unroll
-  for (int u = 0; u < kPerThread; ++u) {
-    const int i = threadIdx.x + u * kThreads;
-    if (i < nvec) {
-      if (kNtStore) __builtin_nontemporal_store(r[u], &d[i]);
-      else d[i] = r[u];
+    for (int u = 0; u < kVectors; ++u) {
+      const int i = threadIdx.x + u * kThreads;
+      if (i < nvec) r[u] = kNt ? __builtin_nontemporal_load(&src[i]) : src[i];
     }
   }
+  template <bool kNt>
+  __device__ __forceinline__ void store(const u32x4 (&r)[kVectors]) const {
+#pragma unroll
+    for (int u = 0; u < kVectors; ++u) {
+      const int i = threadIdx.x + u * kThreads;
+      if (i < nvec) {
+        if (kNt) __builtin_nontemporal_store(r[u], &dst[i]);
+        else dst[i] = r[u];
+      }
+    }
+  }
+};
+
+// One chunk per workgroup.
+template <int kVectors, bool kNtLoad, bool kNtStore>
+__global__ void __launch_bounds__(kThreads)
+state_copy_kernel(const char* __restrict__ src, char* __restrict__ dst, tsattn::CopyList list) {
+  const Chunk<kVectors> c(src, dst, list, blockIdx.x);
+  u32x4 r[kVectors];
+  c.template load<kNtLoad>(r);
+  c.template store<kNtStore>(r);
+}
+
+// Device -> host: workgroup b takes chunks b, b + gridDim.x, ...
+__global__ void __launch_bounds__(kThreads)
+state_suspend_kernel(const char* __restrict__ src, char* __restrict__ dst, tsattn::CopyList list) {
+  constexpr int kVectors = tsattn::kCopyChunkBytes / (kThreads * 16);
+  const int64_t chunks = list.first_chunk[list.n];
+  int64_t i = blockIdx.x;
+  if (i >= chunks) return;
+  u32x4 r[kVectors], ahead[kVectors];
+  Chunk<kVectors> c(src, dst, list, i);
+  c.template load<false>(r);
+  for (i += gridDim.x; i < chunks; i += gridDim.x) {
+    const Chunk<kVectors> next(src, dst, list, i);
+    next.template load<false>(ahead);
+    c.template store<true>(r);
+    c = next;
+#pragma unroll
+    for (int u = 0; u < kVectors; ++u) r[u] = ahead[u];
+  }
+  c.template store<true>(r);
 }
 
 }  // namespace tsstate
@@ -67,17 +115,23 @@ hipError_t launch_state_copy(const void* src, void* dst, const CopyList& list, b
                              bool dst_host, hipStream_t st) {
   const int64_t chunks = list.first_chunk[list.n];
   if (chunks <= 0) return hipSuccess;
+  constexpr int kSmall = kCopyChunkBytes / (tsstate::kThreads * 16);
+  constexpr int kLarge = kHostReadChunkBytes / (tsstate::kThreads * 16);
   const dim3 grid((unsigned)chunks), block(tsstate::kThreads);
   const char* s = (const char*)src;
   char* d = (char*)dst;
   if (src_host && dst_host)
-    hipLaunchKernelGGL((tsstate::state_copy_kernel<true, true>), grid, block, 0, st, s, d, list);
+    hipLaunchKernelGGL((tsstate::state_copy_kernel<kLarge, true, true>), grid, block, 0, st, s, d, list);
   else if (src_host)
-    hipLaunchKernelGGL((tsstate::state_copy_kernel<true, false>), grid, block, 0, st, s, d, list);
+    hipLaunchKernelGGL((tsstate::state_copy_kernel<kLarge, true, false>), grid, block, 0, st, s, d, list);
   else if (dst_host)
-    hipLaunchKernelGGL((tsstate::state_copy_kernel<false, true>), grid, block, 0, st, s, d, list);
+    hipLaunchKernelGGL(tsstate::state_suspend_kernel,
+                       dim3((unsigned)(chunks < tsstate::kWalkers ? chunks : tsstate::kWalkers)), block,
+                       0, st, s, d, list);
+  else if (chunks * kCopyChunkBytes > ((int64_t)32 << 20))
+    hipLaunchKernelGGL((tsstate::state_copy_kernel<kSmall, true, true>), grid, block, 0, st, s, d, list);
   else
-    hipLaunchKernelGGL((tsstate::state_copy_kernel<false, false>), grid, block, 0, st, s, d, list);
+    hipLaunchKernelGGL((tsstate::state_copy_kernel<kSmall, false, false>), grid, block, 0, st, s, d, list);
   return hipGetLastError();
 }
 

@@ -492,7 +492,7 @@ int ts_state_copy(const void* src, int64_t src_bytes, void* dst, int64_t dst_byt
   bool s_host = false, d_host = false;
   if ((rc = copy_operand(src, dev, &s_dev, &s_host)) != TS_OK) return rc;
   if ((rc = copy_operand(dst, dev, &d_dev, &d_host)) != TS_OK) return rc;
-  const int64_t chunk = tsattn::copy_chunk_bytes();
+  const int64_t chunk = tsattn::copy_chunk_bytes(s_host);
   tsattn::CopyList list;
   for (int32_t r0 = 0; r0 < nranges; r0 += tsattn::kMaxCopyRanges) {
     list.n = nranges - r0 < tsattn::kMaxCopyRanges ? nranges - r0 : tsattn::kMaxCopyRanges;
