@@ -2,6 +2,8 @@
 import ctypes
 import os
 
+import torch
+
 from .build import LIB
 
 TS_OK = 0
@@ -56,6 +58,20 @@ def i32(name, x):
     if not -(1 << 31) <= x < (1 << 31):
         raise ValueError("%s = %d does not fit the C ABI's int32" % (name, x))
     return x
+
+
+def i32s(**sizes):
+    """The sizes as C int32 arguments, in order (see i32)."""
+    values = [int(x) for x in sizes.values()]
+    if min(values) < -(1 << 31) or max(values) >= 1 << 31:
+        for name, x in sizes.items():
+            i32(name, x)
+    return values
+
+
+def current_stream(device):
+    """torch's current stream of a GPU device as a hipStream_t value."""
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def status_str(status):

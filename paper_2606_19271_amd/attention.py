@@ -4,8 +4,6 @@ ts_attn_fwd_kvcache_noalloc): argument marshalling only.
 Every step of the computation runs in libts_attn.so on the tensors' device and on torch's current
 stream of that device; nothing here computes attention, and there is no fallback path.
 """
-import ctypes
-
 import numpy as np
 import torch
 
@@ -17,8 +15,14 @@ def default_scale(d):
     return float(np.float32(1.0) / np.sqrt(np.float32(d)))
 
 
-def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr())
+# the scales of the head widths the library takes: numpy's scalar arithmetic costs a small call 3 us
+_SCALES = {d: default_scale(d) for d in (64, 128)}
+
+
+def _scale(scale, d):
+    if scale is None:
+        return _SCALES[d] if d in _SCALES else default_scale(d)
+    return float(scale)
 
 
 def _check_tensor(name, t, ndim):
@@ -26,6 +30,17 @@ def _check_tensor(name, t, ndim):
         raise TypeError("%s must be a torch.Tensor" % name)
     if t.dtype != torch.bfloat16 or t.dim() != ndim or not t.is_cuda or not t.is_contiguous():
         raise ValueError("%s must be a contiguous bfloat16 GPU tensor with %d dims" % (name, ndim))
+
+
+def _call(fn, device, *args):
+    """fn(*args, stream) with `device` current and torch's current stream of it."""
+    if torch.cuda.current_device() == device.index:
+        rc = fn(*args, _lib.current_stream(device))
+    else:
+        with torch.cuda.device(device):
+            rc = fn(*args, _lib.current_stream(device))
+    if rc != _lib.TS_OK:
+        _lib.check(rc)
 
 
 def ts_attn_fwd(q, k, v, scale=None, out=None):
@@ -41,14 +56,8 @@ def ts_attn_fwd(q, k, v, scale=None, out=None):
         _check_tensor("out", out, 4)
         if out.shape != q.shape or out.device != q.device:
             raise ValueError("out must match q")
-    s = default_scale(d) if scale is None else float(scale)
-    lib = _lib.load()
-    with torch.cuda.device(q.device):
-        stream = torch.cuda.current_stream(q.device).cuda_stream
-        rc = lib.ts_attn_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _lib.i32("B", B),
-                             _lib.i32("L", L), _lib.i32("H", H), _lib.i32("d", d), s,
-                             ctypes.c_void_p(stream))
-    _lib.check(rc)
+    _call(_lib.load().ts_attn_fwd, q.device, q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
+          *_lib.i32s(B=B, L=L, H=H, d=d), _scale(scale, d))
     return out
 
 
@@ -71,15 +80,10 @@ def ts_attn_fwd_varlen(q, k, v, cu_seqlens, max_seqlen, scale=None, out=None):
         _check_tensor("out", out, 3)
         if out.shape != q.shape or out.device != q.device:
             raise ValueError("out must match q")
-    s = default_scale(d) if scale is None else float(scale)
-    lib = _lib.load()
-    with torch.cuda.device(q.device):
-        stream = torch.cuda.current_stream(q.device).cuda_stream
-        rc = lib.ts_attn_fwd_varlen(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(cu_seqlens),
-                                    _lib.i32("nseq", cu_seqlens.numel() - 1),
-                                    _lib.i32("max_seqlen", max_seqlen), _lib.i32("T", T),
-                                    _lib.i32("H", H), _lib.i32("d", d), s, ctypes.c_void_p(stream))
-    _lib.check(rc)
+    _call(_lib.load().ts_attn_fwd_varlen, q.device, q.data_ptr(), k.data_ptr(), v.data_ptr(),
+          out.data_ptr(), cu_seqlens.data_ptr(),
+          *_lib.i32s(nseq=cu_seqlens.numel() - 1, max_seqlen=max_seqlen, T=T, H=H, d=d),
+          _scale(scale, d))
     return out
 
 
@@ -138,17 +142,9 @@ def _kvcache(entry, q, k, v, cu_seqlens_q, cu_seqlens_k, max_seqlen_q, max_seqle
         if (not isinstance(lse, torch.Tensor) or lse.dtype != torch.float32 or lse.shape != (Tq, H)
                 or lse.device != q.device or not lse.is_contiguous()):
             raise ValueError("lse must be a contiguous float32 [Tq, H] tensor on q's device")
-    s = default_scale(d) if scale is None else float(scale)
-    lib = _lib.load()
-    with torch.cuda.device(q.device):
-        stream = torch.cuda.current_stream(q.device).cuda_stream
-        rc = getattr(lib, entry)(_ptr(q), _ptr(k), _ptr(v), _ptr(out),
-                                 _ptr(lse) if lse is not None else ctypes.c_void_p(None),
-                                 _ptr(cu_seqlens_q), _ptr(cu_seqlens_k),
-                                 _lib.i32("nseq", cu_seqlens_q.numel() - 1),
-                                 _lib.i32("max_seqlen_q", max_seqlen_q),
-                                 _lib.i32("max_seqlen_k", max_seqlen_k), _lib.i32("Tq", Tq),
-                                 _lib.i32("Tk", Tk), _lib.i32("H", H), _lib.i32("d", d), s,
-                                 _lib.i32("num_splits", num_splits), ctypes.c_void_p(stream))
-    _lib.check(rc)
+    _call(getattr(_lib.load(), entry), q.device, q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
+          None if lse is None else lse.data_ptr(), cu_seqlens_q.data_ptr(), cu_seqlens_k.data_ptr(),
+          *_lib.i32s(nseq=cu_seqlens_q.numel() - 1, max_seqlen_q=max_seqlen_q,
+                     max_seqlen_k=max_seqlen_k, Tq=Tq, Tk=Tk, H=H, d=d),
+          _scale(scale, d), _lib.i32("num_splits", num_splits))
     return (out, lse) if lse is not None else out
