@@ -76,11 +76,11 @@ struct Chunk {
   }
 };
 
-// One chunk per workgroup.
+// One chunk per workgroup: workgroup b takes chunk first + b.
 template <int kVectors, bool kNtLoad, bool kNtStore>
 __global__ void __launch_bounds__(kThreads)
-state_copy_kernel(const char* __restrict__ src, char* __restrict__ dst, tsattn::CopyList list) {
-  const Chunk<kVectors> c(src, dst, list, blockIdx.x);
+state_copy_kernel(const char* __restrict__ src, char* __restrict__ dst, tsattn::CopyList list, int64_t first) {
+  const Chunk<kVectors> c(src, dst, list, first + blockIdx.x);
   u32x4 r[kVectors];
   c.template load<kNtLoad>(r);
   c.template store<kNtStore>(r);
@@ -117,22 +117,28 @@ hipError_t launch_state_copy(const void* src, void* dst, const CopyList& list, b
   if (chunks <= 0) return hipSuccess;
   constexpr int kSmall = kCopyChunkBytes / (tsstate::kThreads * 16);
   constexpr int kLarge = kHostReadChunkBytes / (tsstate::kThreads * 16);
-  const dim3 grid((unsigned)chunks), block(tsstate::kThreads);
+  const dim3 block(tsstate::kThreads);
   const char* s = (const char*)src;
   char* d = (char*)dst;
-  if (src_host && dst_host)
-    hipLaunchKernelGGL((tsstate::state_copy_kernel<kLarge, true, true>), grid, block, 0, st, s, d, list);
-  else if (src_host)
-    hipLaunchKernelGGL((tsstate::state_copy_kernel<kLarge, true, false>), grid, block, 0, st, s, d, list);
-  else if (dst_host)
+  if (dst_host && !src_host) {
     hipLaunchKernelGGL(tsstate::state_suspend_kernel,
                        dim3((unsigned)(chunks < tsstate::kWalkers ? chunks : tsstate::kWalkers)), block,
                        0, st, s, d, list);
-  else if (chunks * kCopyChunkBytes > ((int64_t)32 << 20))
-    hipLaunchKernelGGL((tsstate::state_copy_kernel<kSmall, true, true>), grid, block, 0, st, s, d, list);
-  else
-    hipLaunchKernelGGL((tsstate::state_copy_kernel<kSmall, false, false>), grid, block, 0, st, s, d, list);
-  return hipGetLastError();
+    return hipGetLastError();
+  }
+  auto kern = src_host ? (dst_host ? tsstate::state_copy_kernel<kLarge, true, true>
+                                   : tsstate::state_copy_kernel<kLarge, true, false>)
+              : chunks * kCopyChunkBytes > ((int64_t)32 << 20) ? tsstate::state_copy_kernel<kSmall, true, true>
+                                                               : tsstate::state_copy_kernel<kSmall, false, false>;
+  // a grid holds fewer than 2^32 threads: 2^23 chunks a launch, 128 GiB of 16 KiB ones
+  constexpr int64_t kLaunch = (int64_t)1 << 23;
+  for (int64_t first = 0; first < chunks; first += kLaunch) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)(chunks - first < kLaunch ? chunks - first : kLaunch)), block, 0,
+                       st, s, d, list, first);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace tsattn

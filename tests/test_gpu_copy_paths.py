@@ -43,3 +43,18 @@ def test_copy_paths(where, sizes):
     ts.ts_state_copy(src, dst, ranges)
     torch.cuda.synchronize()
     assert np.array_equal(dst.cpu().numpy(), want)
+
+
+def test_copy_of_more_chunks_than_a_grid_holds():
+    """64 ranges of 2 GiB out of one source: 2^23 chunks of 16 KiB and some more."""
+    n = (2 << 30) + 16
+    if torch.cuda.mem_get_info()[0] < 150 << 30:
+        pytest.skip("needs 150 GiB of device memory")
+    print("[gpu-test] copy of 128 GiB in one list", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    src = torch.randint(-(1 << 62), 1 << 62, ((n + 64 * 16) // 8,), generator=g, device="cuda").view(torch.uint8)
+    dst = torch.empty(64 * n, dtype=torch.uint8, device="cuda")
+    ranges = [(16 * r, n * r, n) for r in range(64)]
+    ts.ts_state_copy(src, dst, ranges)
+    for s, d, n in ranges:
+        assert torch.equal(dst[d:d + n].view(torch.int64), src[s:s + n].view(torch.int64))
