@@ -1148,8 +1148,9 @@ __device__ __forceinline__ void run_thin_item(const Item& it, const __bf16* __re
 //    32 c + 0..31 of both query blocks, at d = 64 channels 32 (c & 1) + 0..31 of query block c >> 1.
 //    One consumer per query block sums its weights (row_sums).
 // Each SIMD holds one producer and one consumer, so the exponentials run under the other's MFMAs.
-// One barrier per tile.  The producers fetch K (K_{j+3} in phase j), the consumers V (V_{j+1}), into
-// rings of three stages; each wave waits for its previous phase's fetch before the barrier.
+// One barrier per tile.  The producers fetch K (K_{j+4} in phase j, into a ring of four stages), the
+// consumers V (V_{j+1}, a ring of three); each wave waits for its previous phase's fetch before the
+// barrier.
 //
 // Every score, weight, product and sum is formed by the same instructions in the same order as in
 // run_item_group -- the softmax's decisions are taken per 32 queries and key tile there too -- so the
