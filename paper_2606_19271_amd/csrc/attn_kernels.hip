@@ -1232,6 +1232,9 @@ __device__ __forceinline__ void run_small_item(const Item& it, const __bf16* __r
 
   // prologue: the queries (64 rows, 1 KiB per instruction, in the weight buffers), K_0 .. K_2, V_0
   int koff[G::kKDmaMax], voff[G::kVDmaPerWave];
+  // The first barrier waits for the queries and K_0 only, the second for K_1 and K_2, phase 0 for the rest
+  // (all of it before the first barrier: three 256-query chunks at d = 64 14.67 us against 14.51, 1024
+  // keys x 2 heads 10.26 against 10.12; the same in run_item_group gained nothing).
   if (producer) {
     dma_offsets_k<D>(gw, lane, row_bytes, koff);
     dma_k<D>(rk, key0(0), row_bytes, ktile(0), koff, gw);
@@ -1255,7 +1258,9 @@ __device__ __forceinline__ void run_small_item(const Item& it, const __bf16* __r
   }
   if (tid < 2) flags[tid] = 0;
   wait_lds();
-  wait_vmem<0>();
+  static_assert(G::kKStages == 4, "K_1 .. K_3 outstanding");
+  if (producer) wait_vmem<3 * G::kKDmaMin>();
+  else wait_vmem<G::kVDmaPerWave>();
   block_sync();
 
   float l_tot[2] = {0.0f, 0.0f};  // of a summing consumer: its block's row sums
@@ -1392,9 +1397,10 @@ __device__ __forceinline__ void run_small_item(const Item& it, const __bf16* __r
     bf16x8 k0[D / 16], k1[D / 16];  // K fragments of the next two score blocks
     read_k(0, k1);
     scores(k1, s0);
-    read_k(1, k0);
+    wait_vmem<G::kKDmaMin>();
     wait_lds();
     block_sync();  // phase 0 refills K_0's stage
+    read_k(1, k0);
     int j = 0;
     for (; j + 2 <= ntiles; j += 2) {
       phase(j, s0, s1, k0, k1);
