@@ -136,7 +136,8 @@ int ts_attn_fwd_varlen(const void* q, const void* k, const void* v, void* o,
  *  cu_seqlens_q/k  DEVICE int32, nseq+1 entries each: start at 0, nondecreasing, end at
  *                  total_q / total_k.  Empty segments are allowed on either side.
  *  max_seqlen_q/k  upper bounds of the segment lengths (host values; size the launch)
- *  num_splits      0: chosen by the library.  n in 1..16: every (segment, head, 256-query tile)
+ *  num_splits      0: chosen by the library, from total_q, max_seqlen_k, H, d and the number of
+ *                  CUs (and, without allocation, what fits: see below).  n in 1..16: every (segment, head, 256-query tile)
  *                  is split into n consecutive key ranges run by separate workgroups, and a
  *                  second kernel merges their results by their log-sum-exp.  Splitting fills
  *                  the GPU when there are few query tiles (short chunks, long caches).  The
@@ -168,8 +169,8 @@ int ts_attn_fwd_kvcache(const void* q, const void* k, const void* v, void* o, fl
  *    ends), not in a per-call allocation.  A call needs
  *      align256(4 * (2 nseq + 2)) + [n > 1] (align256(4 n total_q H) + 4 n total_q H d)
  *    bytes for n key ranges.  A forced num_splits whose partials do not fit returns
- *    TS_ERR_SCRATCH before any HIP call; num_splits = 0 takes the library's choice among the n
- *    that fit (n = 1 always fits).
+ *    TS_ERR_SCRATCH before any HIP call; num_splits = 0 takes the library's choice, lowered to
+ *    the largest n that fits (n = 1 always fits).
  *  - Races: every call on a device shares that device's array, and a call leaves its contents
  *    behind.  Calls on one stream are ordered; calls that may overlap on one device (different
  *    streams, or host threads without ordering between their streams) race on the array and give

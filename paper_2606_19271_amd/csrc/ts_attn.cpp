@@ -19,7 +19,6 @@ namespace {
 constexpr int kMaxDevices = 64;
 constexpr int64_t kByteLimit = (int64_t)1 << 31;
 constexpr int64_t kGridLimit = (int64_t)1 << 23;  // workgroups per launch (x 512 threads < 2^32)
-constexpr int32_t kMaxSplits = 16;                 // key ranges per query tile of a split call
 
 struct DeviceState {
   std::once_flag once;
@@ -186,10 +185,6 @@ int check_kv(const void* q, const void* k, const void* v, const void* o, const f
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Workspaces up to this size come from the device's cached workspace; larger ones (long split
-// calls) from a stream-ordered pool allocation of their own.
-constexpr size_t kWorkspaceCache = (size_t)256 << 20;
-
 // Bytes of device scratch a packed call needs: the plan and, with n > 1 key ranges, the float32
 // partial lse [n][tq][H] and O [n][tq][H][d], each part 256-byte aligned.
 int64_t scratch_bytes(int32_t nseq, int32_t n, int32_t tq, int32_t H, int32_t d) {
@@ -199,14 +194,6 @@ int64_t scratch_bytes(int32_t nseq, int32_t n, int32_t tq, int32_t H, int32_t d)
     b += (int64_t)n * tq * H * d * (int64_t)sizeof(float);
   }
   return b;
-}
-
-// The library's choice of key ranges for a call whose scratch must not exceed `limit` bytes (one range
-// is always allowed).
-int32_t choose_splits(const tsattn::PackedArgs& a, int64_t limit, int32_t cus) {
-  int32_t max_n = kMaxSplits;
-  while (max_n > 1 && scratch_bytes(a.nseq, max_n, a.total_q, a.H, a.d) > limit) --max_n;
-  return tsattn::auto_splits({a.nseq, a.total_q, a.total_k, a.max_k, a.H, a.d}, max_n, cus);
 }
 
 // Points a.plan (and, for a split call, a.part_lse / a.part_o) into buf, laid out as in
@@ -254,6 +241,10 @@ int launch_with(tsattn::PackedArgs a, char* buf, bool without_plan, bool validat
   }
   return rc;
 }
+
+// Workspaces up to this size come from the device's cached workspace; larger ones (long split
+// calls) from a stream-ordered pool allocation of their own.
+constexpr size_t kWorkspaceCache = (size_t)256 << 20;
 
 int run_packed(DeviceState* st, tsattn::PackedArgs a, hipStream_t s) {
   const bool validate = validate_mode();
@@ -315,10 +306,10 @@ int check_kvcache_call(const void* q, const void* k, const void* v, const void* 
                        int32_t nseq, int32_t max_seqlen_q, int32_t max_seqlen_k, int32_t total_q,
                        int32_t total_k, int32_t H, int32_t d, float scale, int32_t num_splits) {
   if (!cu_seqlens_q || !cu_seqlens_k) return TS_ERR_NULL;
-  if (nseq < 0 || num_splits < 0 || num_splits > kMaxSplits) return TS_ERR_SHAPE;
+  if (nseq < 0 || num_splits < 0 || num_splits > tsattn::kMaxSplits) return TS_ERR_SHAPE;
   int rc = check_kv(q, k, v, o, lse, total_q, total_k, max_seqlen_q, max_seqlen_k, H, d, scale);
   if (rc != TS_OK) return rc;
-  if (tsattn::packed_grid_bound(total_q, nseq, H, kMaxSplits) >= kGridLimit) return TS_ERR_SHAPE;
+  if (tsattn::packed_grid_bound(total_q, nseq, H, tsattn::kMaxSplits) >= kGridLimit) return TS_ERR_SHAPE;
   if (tsattn::merge_blocks(total_q, H, d) >= ((int64_t)1 << 31)) return TS_ERR_SHAPE;
   return TS_OK;
 }
@@ -349,12 +340,13 @@ int copy_operand(const void* p, int dev, const void** devp, bool* host) {
 
 // A packed or chunk call on the device's static scratch array: the allocation-free entry point,
 // and the allocating ones on a capturing stream (where the workspace's event waits and growth, or
-// a pool allocation, have no place).  n = 0 takes the library's choice among the n whose partial
+// a pool allocation, have no place).  n = 0 takes the library's choice, lowered until its partial
 // results fit the scratch; a forced n that does not fit returns TS_ERR_SCRATCH.  Validation mode
 // does not apply: invalid offsets make the call a device-side no-op.
 int run_static(DeviceState* st, tsattn::PackedArgs a, int32_t n, hipStream_t s) {
   if (n == 0) {
-    n = choose_splits(a, tsattn::kScratchBytes, st->cus);
+    n = tsattn::auto_splits(a.total_q, a.max_k, a.H, a.d, st->cus);
+    while (n > 1 && scratch_bytes(a.nseq, n, a.total_q, a.H, a.d) > tsattn::kScratchBytes) --n;
   } else if (scratch_bytes(a.nseq, n, a.total_q, a.H, a.d) > tsattn::kScratchBytes) {
     return TS_ERR_SCRATCH;
   }
@@ -442,8 +434,8 @@ int ts_attn_fwd_kvcache(const void* q, const void* k, const void* v, void* o, fl
                        max_seqlen_k, total_q, total_k, H, d, 1, scale, st->xcd_chunk,
                        nullptr, nullptr, nullptr, false};
   if (capturing((hipStream_t)stream)) return run_static(st, a, num_splits, (hipStream_t)stream);
-  // (within the cached workspace: beyond it the pool makes the host wait)
-  a.n_split = num_splits > 0 ? num_splits : choose_splits(a, kWorkspaceCache, st->cus);
+  a.n_split =
+      num_splits > 0 ? num_splits : tsattn::auto_splits(total_q, max_seqlen_k, H, d, st->cus);
   return run_packed(st, a, (hipStream_t)stream);
 }
 

@@ -144,3 +144,29 @@ def test_bad_offsets_are_a_no_op_without_a_plan():
             ts.ts_attn_fwd_kvcache(q, k, v, c, c, 300, 300, out=out, lse=lse, num_splits=splits)
             torch.cuda.synchronize()
             assert bool((out == 7.0).all()) and bool((lse == 7.0).all()), (cu, splits)
+
+
+# chunks against caches of even and uneven length, and the key ranges that the library takes for them
+CHOICES = [((256, 256, 256, 256), (1536, 512, 1280, 1536), 4, 64, 3), ((768,), (2816,), 12, 128, 7),
+           ((768, 256, 256, 768, 256, 768), (1024, 4608, 1536, 1280, 1536, 1024), 12, 128, 12),
+           ((256,) * 4, (5120,) * 4, 16, 128, 4), ((1560, 1560), (7800, 4680), 4, 64, 9), ((256,), (5376,), 16, 64, 9),
+           ((500, 500), (400, 400), 2, 128, 1)]
+
+
+@pytest.mark.parametrize("lq,lk,H,d,n", CHOICES, ids=str)
+def test_automatic_key_ranges(lq, lk, H, d, n):
+    """num_splits = 0 gives the bits of the n it stands for; without allocation, of the most ranges up to
+    n whose float32 partial results fit the scratch array."""
+    q, _, _ = draw(sum(lq), 1, H, d, 11, "normal")
+    _, k, v = draw(1, sum(lk), H, d, 12, "normal")
+    cq, ck = (torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32, device="cuda") for x in (lq, lk))
+    args = (q.cuda(), k.cuda(), v.cuda(), cq, ck, max(lq), max(lk))
+    fits = n
+    while fits > 1 and 4 * fits * sum(lq) * H * (d + 1) + 1024 > 32 << 20:
+        fits -= 1
+    say("automatic key ranges", lq, lk, H, d, n, fits)
+    for entry, ranges in ((ts.ts_attn_fwd_kvcache, n), (ts.ts_attn_fwd_kvcache_noalloc, fits)):
+        want, want_lse = ts.ts_attn_fwd_kvcache(*args, return_lse=True, num_splits=ranges)
+        o, lse = entry(*args, return_lse=True, num_splits=0)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(o), bits(want)) and torch.equal(bits(lse), bits(want_lse)), entry

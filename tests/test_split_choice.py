@@ -23,17 +23,21 @@ int main() {
   auto rnd = [&](int64_t n) { r = r * 6364136223846793005ull + 1442695040888963407ull; return (int64_t)(r >> 33) % n; };
   const int32_t big[] = {0, 1, 63, 64, 65, 255, 256, 257, 32760, 8388607};
   for (int i = 0; i < 200000; ++i) {
-    SplitShape c;
+    struct { int32_t nseq, total_q, max_k, H, d; } c;
     c.nseq = 1 + (int32_t)(rnd(3) ? rnd(70) : rnd(100000));
     c.total_q = rnd(4) ? (int32_t)rnd(200000) : big[rnd(10)];
-    c.total_k = rnd(4) ? (int32_t)rnd(2000000) : big[rnd(10)];
     c.max_k = rnd(4) ? (int32_t)rnd(100000) : big[rnd(10)];
     c.H = 1 + (int32_t)rnd(128);
     c.d = rnd(2) ? 64 : 128;
-    const int32_t max_n = 1 + (int32_t)rnd(16);
-    const int32_t n = auto_splits(c, max_n, 256);
+    const int32_t n = auto_splits(c.total_q, c.max_k, c.H, c.d, 256);
     const int64_t tiles = ((int64_t)c.max_k + key_tile(c.d) - 1) / key_tile(c.d);
-    CHECK(n >= 1 && n <= max_n && (n == 1 || tiles / n >= 4));
+    CHECK(n >= 1 && n <= 16 && (n == 1 || tiles / n >= 4));
+    // the fewest rounds of key tiles, then the fewest ranges; grids that fill the GPU stay whole
+    const int64_t q_items = (int64_t)c.H * ((c.total_q + 255ll) / 256);
+    auto rounds = [&](int64_t m) { return (q_items * m + 255) / 256 * ((tiles + m - 1) / m); };
+    if (q_items == 0 || q_items >= 256 || tiles < 8) CHECK(n == 1);
+    else
+      for (int32_t m = 1; m <= 16 && tiles / m >= 4; ++m) CHECK(m < n ? rounds(m) > rounds(n) : rounds(m) >= rounds(n));
     // the launch grid holds every item, whatever the lengths: equal ones, and all but one empty
     const int32_t tile = rnd(2) ? kSmallTile : kQueryTile;
     const int64_t per = (int64_t)c.H * n, t = tile;
@@ -44,8 +48,12 @@ int main() {
     CHECK(packed_items(c.total_q, c.nseq, c.H, n, kQueryTile) <= packed_grid_bound(c.total_q, c.nseq, c.H, n));
   }
   // a call that fills the GPU for many rounds is not split; one 24-item call over 512 tiles is
-  CHECK(auto_splits({1, 32760, 32760, 32760, 40, 128}, 16, 256) == 1);
-  CHECK(auto_splits({1, 500, 32760, 32760, 12, 128}, 16, 256) > 4);
+  CHECK(auto_splits(32760, 32760, 40, 128, 256) == 1);
+  CHECK(auto_splits(500, 32760, 12, 128, 256) > 4);
+  // equal sessions, single chunks, and uneven ones: total queries, longest cache, heads, d -> ranges
+  const int32_t known[][5] = {{1024, 1536, 4, 64, 3}, {768, 2816, 12, 128, 7}, {3072, 4608, 12, 128, 12}, {1024, 5120, 16, 128, 4},
+                              {1280, 5120, 12, 64, 4}, {512, 5120, 16, 128, 8}, {1560, 32760, 12, 128, 3}, {768, 2304, 4, 64, 4}};
+  for (const auto& w : known) CHECK(auto_splits(w[0], w[1], w[2], w[3], 256) == w[4]);
   CHECK(!small_items(257, 4096, 256) && small_items(256, 4096, 256) && !small_items(1, 64, 256));
   printf("failures %d\n", bad);
   return bad != 0;
