@@ -103,10 +103,12 @@ int ts_attn_fwd(const void* q, const void* k, const void* v, void* o, int32_t B,
  * unwritten); with the environment variable TS_ATTN_VALIDATE=1 the call instead synchronizes
  * on stream and returns TS_ERR_SEGMENTS.
  * Work scheduling: segments run longest first, so uneven batches finish with a short tail.
- * Up to 64 segments are checked and ordered by the attention kernel itself, without any device
- * memory (but not in validation mode); for larger batches a small planning kernel runs first and
- * the attention kernel walks its plan, which lives in a device workspace the library keeps per device (grown when a call needs more, up to
- * 256 MiB, and held until the process ends; TS_ERR_NOMEM if it cannot be grown).  The calls
+ * One segment, or up to 64 in few work items, are checked and ordered by the attention kernel
+ * itself, without any device memory (but not in validation mode): at most 96 segments x work items
+ * per CU, so 64 segments in 1.5 items a CU, 8 in 12.  For other batches a small planning kernel runs
+ * first and the attention kernel walks its plan, which lives in a device workspace the library keeps
+ * per device (grown when a call needs more, up to 256 MiB, and held until the process ends;
+ * TS_ERR_NOMEM if it cannot be grown).  The calls
  * that use it take it in turn: each one's stream waits on the GPU for an event recorded after
  * the previous one, so the host never waits, calls on one stream keep their order, and such
  * calls on different streams run one after the other.  For one segment (nseq = 1) a total above
@@ -148,8 +150,9 @@ int ts_attn_fwd_varlen(const void* q, const void* k, const void* v, void* o,
  * Device memory: the plan and, for n > 1, float32 partial results (n * total_q * H * (d + 1)
  * floats) come from the workspace of ts_attn_fwd_varlen, or, when they exceed its 256 MiB,
  * from a stream-ordered pool allocation made and released by the call (TS_ERR_NOMEM if it
- * cannot be made; HIP's pool makes the host wait for the stream there); a call of up to 64 segments
- * needs no plan, and unsplit no device memory at all (as in ts_attn_fwd_varlen).  Bad
+ * cannot be made; HIP's pool makes the host wait for the stream there); a call whose segments the
+ * attention kernel orders itself needs no plan, and unsplit no device memory at all (as in
+ * ts_attn_fwd_varlen).  Bad
  * offsets behave as in ts_attn_fwd_varlen (a device no-op, or TS_ERR_SEGMENTS under
  * TS_ATTN_VALIDATE=1).  num_splits outside 0..16 and the size
  * limits above (for max_seqlen_q and max_seqlen_k each) give TS_ERR_SHAPE.

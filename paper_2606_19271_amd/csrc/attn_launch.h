@@ -32,8 +32,8 @@ struct PackedArgs {
   int32_t nseq, max_q, max_k, total_q, total_k, H, d, n_split;
   float scale;
   int xcd_chunk;
-  int32_t* plan;         // device, plan_ints(nseq) entries; null for a batch of at most
-                         // kWavePlanSegs segments run without the planning kernel
+  int32_t* plan;         // device, plan_ints(nseq) entries; null for a batch run without the
+                         // planning kernel (wave_plan)
   float* part_o;         // device [n_split][total_q][H][d] (n_split > 1)
   float* part_lse;       // device [n_split][total_q][H] (n_split > 1)
   bool small;            // 64-query items (small_items)
@@ -42,7 +42,7 @@ struct PackedArgs {
 // Sizes shared by the kernels and the host-side planning (attn_plan.cpp).
 constexpr int kQueryTile = 256;             // queries per work item of the attention kernels
 constexpr int kSmallTile = 64;              // and of their variants for small grids
-constexpr int kWavePlanSegs = 64;           // segments that a wave plans by itself, one per lane
+constexpr int kWavePlanSegs = 64;           // most segments that a wave plans by itself, one per lane
 constexpr int32_t kMaxSplits = 16;          // key ranges per query tile of a split call
 constexpr int kMergeThreads = 256;          // threads per workgroup of the merge kernel
 // Keys per K/V tile of the attention kernels at head width d (64 or 128).
@@ -60,6 +60,9 @@ int64_t packed_items(int32_t total_q, int32_t nseq, int32_t H, int32_t n_split, 
 // Whether a call of at most `items` 64-query work items, over at most max_k keys each, runs in those
 // instead of 256-query ones.
 bool small_items(int64_t items, int32_t max_k, int32_t cus);
+// Whether a packed call of at most `items` work items runs without the planning kernel, every wave
+// finding its item's segment itself.
+bool wave_plan(int32_t nseq, int64_t items, int32_t cus);
 // Key ranges per query tile when the caller leaves the choice to the library.  One workgroup runs per
 // CU, so `items` 256-query items take ceil(items / cus) rounds, each as long as one item's key tiles.
 // Query tiles that already fill the GPU are not split (the partials would only add traffic);

@@ -2,6 +2,8 @@
 // the argument checks of ts_attn.cpp and the launch code; no device code.
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "attn_launch.h"
 
 namespace tsattn {
@@ -22,6 +24,14 @@ int64_t packed_items(int32_t total_q, int32_t nseq, int32_t H, int32_t n_split, 
 // two rounds they lose: 18 heads 20.3 against 17.5 us and 26.1 against 21.6.  Up to 64 keys there is
 // nothing to split (4.65 against 4.7 us at d = 64, 4.8 against 4.4 at d = 128).
 bool small_items(int64_t items, int32_t max_k, int32_t cus) { return items <= cus && max_k > 64; }
+
+// A wave's own plan costs each round of items 0.085 us a segment, and saves the planning kernel, 4 to
+// 7 us a call.  Measured over 2 to 64 segments and up to 40 rounds (us with the wave's plan and with the
+// kernel's): 8 segments in 5 rounds 109.8 and 112.6, 12 in 7.5 167.9 and 168.8, 24 in 7.5 53.0 and
+// 47.1, 64 in 10 115.8 and 60.0; the two meet at about 110 segments x rounds.
+bool wave_plan(int32_t nseq, int64_t items, int32_t cus) {
+  return nseq == 1 || (nseq <= kWavePlanSegs && nseq * std::max<int64_t>(items, cus) <= (int64_t)96 * cus);
+}
 
 int32_t auto_splits(int32_t total_q, int32_t max_k, int32_t H, int32_t d, int32_t cus) {
   const int64_t items = (int64_t)H * (((int64_t)total_q + kQueryTile - 1) / kQueryTile);

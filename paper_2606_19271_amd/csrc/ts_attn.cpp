@@ -208,11 +208,6 @@ void carve(tsattn::PackedArgs& a, char* buf) {
   }
 }
 
-// A batch of at most kWavePlanSegs segments runs without the planning kernel: the attention and merge
-// kernels check its offsets themselves (a mismatch makes the call a device-side no-op, as a rejected
-// plan does).
-bool planless(const tsattn::PackedArgs& a) { return a.nseq <= tsattn::kWavePlanSegs; }
-
 // With one segment, totals beyond the stated maximum lengths admit no valid offsets at all: such a
 // call is a no-op without any device work.
 bool no_valid_offsets(const tsattn::PackedArgs& a) {
@@ -223,6 +218,14 @@ bool no_valid_offsets(const tsattn::PackedArgs& a) {
 bool small_tiles(const tsattn::PackedArgs& a, int32_t cus) {
   return tsattn::small_items(
       tsattn::packed_items(a.total_q, a.nseq, a.H, a.n_split, tsattn::kSmallTile), a.max_k, cus);
+}
+
+// Whether the call runs without the planning kernel (a.n_split and a.small are set): the attention and
+// merge kernels check its offsets themselves (a mismatch makes the call a device-side no-op, as a
+// rejected plan does).
+bool planless(const tsattn::PackedArgs& a, int32_t cus) {
+  const int32_t tile = a.small ? tsattn::kSmallTile : tsattn::kQueryTile;
+  return tsattn::wave_plan(a.nseq, tsattn::packed_items(a.total_q, a.nseq, a.H, a.n_split, tile), cus);
 }
 
 // Launch of a packed call whose plan (and partials) sit in buf, and the validation-mode read-back
@@ -249,8 +252,8 @@ constexpr size_t kWorkspaceCache = (size_t)256 << 20;
 int run_packed(DeviceState* st, tsattn::PackedArgs a, hipStream_t s) {
   const bool validate = validate_mode();
   // validation mode keeps the plan, whose error flag it reads back
-  const bool without_plan = planless(a) && !validate;
   a.small = small_tiles(a, st->cus);
+  const bool without_plan = planless(a, st->cus) && !validate;
   if (without_plan) {
     if (no_valid_offsets(a)) return TS_OK;
     if (a.n_split == 1) {  // no device memory at all
@@ -353,7 +356,7 @@ int run_static(DeviceState* st, tsattn::PackedArgs a, int32_t n, hipStream_t s) 
   a.n_split = n;
   a.small = small_tiles(a, st->cus);
   carve(a, (char*)st->scratch);
-  if (planless(a)) {
+  if (planless(a, st->cus)) {
     if (no_valid_offsets(a)) return TS_OK;
     a.plan = nullptr;
   }

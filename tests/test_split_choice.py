@@ -55,6 +55,10 @@ int main() {
                               {1280, 5120, 12, 64, 4}, {512, 5120, 16, 128, 8}, {1560, 32760, 12, 128, 3}, {768, 2304, 4, 64, 4}};
   for (const auto& w : known) CHECK(auto_splits(w[0], w[1], w[2], w[3], 256) == w[4]);
   CHECK(!small_items(257, 4096, 256) && small_items(256, 4096, 256) && !small_items(1, 64, 256));
+  // the waves' own plan: at most 96 segments x rounds of items, one segment always
+  CHECK(wave_plan(1, 1 << 23, 256) && wave_plan(64, 1, 256) && wave_plan(64, 384, 256) && !wave_plan(64, 385, 256));
+  CHECK(!wave_plan(65, 1, 256) && !wave_plan(64, 2560, 256) && !wave_plan(32, 1280, 256) && !wave_plan(48, 1920, 256));
+  CHECK(wave_plan(8, 1280, 256) && wave_plan(2, 12288, 256) && !wave_plan(2, 12289, 256) && !wave_plan(64, 1 << 23, 256));
   printf("failures %d\n", bad);
   return bad != 0;
 }
