@@ -391,7 +391,10 @@ constexpr float kBias = 39.0f;
 // weights against m_c = -inf are all infinite, so an attempt with the running maximum never holds
 // (skipping it saves 620 clocks per group at d = 128 and 1200 at d = 64, of an item's two first
 // vector steps).  The last one is masked: its keys past the segment's end score -inf, so their
-// weights are exactly 0 (c > 0, see softmax_factor).
+// weights are exactly 0 (c > 0).  With scale 0 (c = 0) no score can do that, because one that is not
+// finite makes its row NaN: there the last tile is not masked, and the keys past the end have the
+// weight of every key, rows of V that are zeros, and a part of the row sum that is taken out again
+// (their K rows are zeros too, so they make no row NaN that its own keys do not).
 enum TileKind { kFirstTile = 0, kInnerTile = 1, kLastTile = 2 };
 
 // issue(0 .. kIssue - 1): instructions to spread over the tile's exp work (see exp_pack); all
@@ -638,7 +641,7 @@ __device__ __forceinline__ void write_result(const Item& it, const Out& out,
 // barrier, so the workgroup's schedule is unchanged, but it skips the MFMA, softmax and LDS-read
 // work and writes nothing.  Under the power cap the idle matrix and vector work is worth clock
 // to the rest of the chip.
-template <int D, bool kGroupB, int kMode, bool kActive>
+template <int D, bool kGroupB, int kMode, bool kActive, bool kScale0>
 __device__ __forceinline__ void run_item_group(const Item& it, const __bf16* __restrict__ q,
                                                const __bf16* __restrict__ k,
                                                const __bf16* __restrict__ v, const Out& out,
@@ -705,7 +708,8 @@ __device__ __forceinline__ void run_item_group(const Item& it, const __bf16* __r
 
   const int ntiles = it.ntiles;
   // valid keys of the item's last tile: fewer than kBN only on the segment's ragged last tile
-  const int last_keys = min(kBN, it.k_len - (it.tile_begin + ntiles - 1) * kBN);
+  const int end_keys = min(kBN, it.k_len - (it.tile_begin + ntiles - 1) * kBN);
+  const int last_keys = kScale0 ? kBN : end_keys;
   // vector step j: fetch tile j + kFetchAhead (a V tile into stage vst2 = (j + 2) % 3), its
   // instructions spread over the softmax S_j -> P_j, wait for the fetch of the previous vector
   // step, read the first K fragments of
@@ -783,9 +787,13 @@ __device__ __forceinline__ void run_item_group(const Item& it, const __bf16* __r
   if (!kGroupB) block_sync();  // matches group B's extra barrier at the start
   wait_vmem<0>();  // the fetches past the end must land before the workgroup leaves
 
-  if constexpr (kActive)
-    write_result<D, kMode>(it, out, oacc, lacc[0][0] + lacc[1][0], m_c, H, it.q_begin + 32 * wave,
+  if constexpr (kActive) {
+    float l_tot = lacc[0][0] + lacc[1][0];
+    // exact: every weight is the same power of two
+    if constexpr (kScale0) l_tot -= (float)(kBN - end_keys) * __builtin_amdgcn_exp2f(-kBias);
+    write_result<D, kMode>(it, out, oacc, l_tot, m_c, H, it.q_begin + 32 * wave,
                            lds + G::kOBase + wave * G::kOWave, lane);
+  }
 }
 
 // The epilogue of one wave: O = O / l for its 32 query rows (the first is q0, relative to the
@@ -1580,8 +1588,10 @@ __device__ __forceinline__ void write_empty(const Item& it, const Out& out, int 
 }
 
 // kThin = false compiles the thin path out, for launches that have no query tile of at most
-// kThinQueries queries (the full tiles' code is then exactly that of a build without it).
-template <int D, int kMode, bool kThin = true>
+// kThinQueries queries (the full tiles' code is then exactly that of a build without it).  kScale0:
+// scale 0, in kernels of its own for the same reason: with the choice made at run time the large
+// calls, whose loops do not change but move, were 1 % slower.
+template <int D, int kMode, bool kThin, bool kScale0>
 __device__ __forceinline__ void run_item(const Item& it, const __bf16* __restrict__ q,
                                          const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                                          const Out& out, int H, float c, bool negate_q, char* smem) {
@@ -1596,16 +1606,16 @@ __device__ __forceinline__ void run_item(const Item& it, const __bf16* __restric
   }
   const bool active = it.q_begin + 32 * wave < it.q_len;  // some query of this wave is in range
   if (wave >= kWaves / 2) {
-    if (active) run_item_group<D, true, kMode, true>(it, q, k, v, out, H, c, negate_q, smem);
-    else run_item_group<D, true, kMode, false>(it, q, k, v, out, H, c, negate_q, smem);
+    if (active) run_item_group<D, true, kMode, true, kScale0>(it, q, k, v, out, H, c, negate_q, smem);
+    else run_item_group<D, true, kMode, false, kScale0>(it, q, k, v, out, H, c, negate_q, smem);
   } else {
-    if (active) run_item_group<D, false, kMode, true>(it, q, k, v, out, H, c, negate_q, smem);
-    else run_item_group<D, false, kMode, false>(it, q, k, v, out, H, c, negate_q, smem);
+    if (active) run_item_group<D, false, kMode, true, kScale0>(it, q, k, v, out, H, c, negate_q, smem);
+    else run_item_group<D, false, kMode, false, kScale0>(it, q, k, v, out, H, c, negate_q, smem);
   }
 }
 
 // kThin: L mod kBM is in 1..kThinQueries, so the last query tile of every sequence is thin.
-template <int D, bool kThin>
+template <int D, bool kThin, bool kScale0>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attn_dense_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                   const __bf16* __restrict__ v, __bf16* __restrict__ o, int L, int H, int nq,
@@ -1631,7 +1641,7 @@ attn_dense_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   it.tile_begin = 0;
   it.ntiles = (L + Geo<D>::kBN - 1) / Geo<D>::kBN;
   Out out{o, nullptr, nullptr, nullptr, 0, 0};
-  run_item<D, kFinal, kThin>(it, q, k, v, out, H, c, negate_q != 0, smem);
+  run_item<D, kFinal, kThin, kScale0>(it, q, k, v, out, H, c, negate_q != 0, smem);
 }
 
 // A 64-query item.  Query tiles that the 256-query kernel runs as thin items are run as such here too,
@@ -1725,8 +1735,8 @@ __device__ __forceinline__ int small_div(int n, int d) {
   return q;
 }
 
-// kSmall: 64-query items (run_small_item).
-template <int D, int kMode, bool kSmall>
+// kSmall: 64-query items (run_small_item), never with scale 0.
+template <int D, int kMode, bool kSmall, bool kScale0>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attn_varlen_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                    const __bf16* __restrict__ v, Out out, const int32_t* __restrict__ cu_q,
@@ -1782,7 +1792,7 @@ attn_varlen_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   it.ntiles = max(0, min(per_split, seg_tiles - it.tile_begin));
   out.split = split;
   if constexpr (kSmall) run_small_or_thin<D, kMode>(it, q, k, v, out, H, c, negate_q != 0, smem);
-  else run_item<D, kMode>(it, q, k, v, out, H, c, negate_q != 0, smem);
+  else run_item<D, kMode, true, kScale0>(it, q, k, v, out, H, c, negate_q != 0, smem);
 }
 
 // Combines the key ranges of a split call: for every (query row, head) with partial results
@@ -1908,19 +1918,12 @@ plan_kernel(const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, 
 // ---------------------------------------------------------------------------------------------
 // host-side launchers
 
-// The factor of the scores in the exponent, |scale| log2(e) (a negative scale flips Q's signs).  It
-// is kept positive, so that a masked score of -inf has weight 0: scale 0 takes the least subnormal,
-// whose product with any finite score, below 4.8e-7, is less than half an ulp of m_c = kBias.
-static float softmax_factor(float scale) {
-  const float c = fabsf(scale) * kLog2e;
-  return c > 0.0f ? c : 1.401298464e-45f;
-}
-
+// The factor of the scores in the exponent is |scale| log2(e) (a negative scale flips Q's signs).
 template <int D>
 static hipError_t launch_dense_d(const DenseArgs& a, hipStream_t st) {
   const int nq = (a.L + kBM - 1) / kBM;
   const int total = a.B * a.H * nq;
-  const float c = softmax_factor(a.scale);
+  const float c = fabsf(a.scale) * kLog2e;
   if (a.small) {
     const int n = (a.L + kSmallTile - 1) / kSmallTile, total_small = a.B * a.H * n;
     hipLaunchKernelGGL(attn_dense_small_kernel<D>, dim3(total_small), dim3(kThreads), SmallGeo<D>::kLds,
@@ -1929,8 +1932,9 @@ static hipError_t launch_dense_d(const DenseArgs& a, hipStream_t st) {
     return hipGetLastError();
   }
   const int tail = a.L % kBM;
-  auto kern = tail != 0 && tail <= kThinQueries ? attn_dense_kernel<D, true>
-                                                : attn_dense_kernel<D, false>;
+  auto kern = a.scale == 0.0f                     ? attn_dense_kernel<D, true, true>
+              : tail != 0 && tail <= kThinQueries ? attn_dense_kernel<D, true, false>
+                                                  : attn_dense_kernel<D, false, false>;
   hipLaunchKernelGGL(kern, dim3(total), dim3(kThreads), Geo<D>::kLds, st, (const __bf16*)a.q,
                      (const __bf16*)a.k, (const __bf16*)a.v, (__bf16*)a.o, a.L, a.H, nq,
                      main_query_tiles(a.L), total, a.xcd_chunk, c, a.scale < 0.0f ? 1 : 0);
@@ -1948,12 +1952,16 @@ static hipError_t launch_packed_d(const PackedArgs& a, hipStream_t st) {
     if (e != hipSuccess) return e;
   }
   const int64_t grid = packed_items(a.total_q, a.nseq, a.H, a.n_split, tile);
-  const float c = softmax_factor(a.scale);
+  const float c = fabsf(a.scale) * kLog2e;
   const int neg = a.scale < 0.0f ? 1 : 0;
   Out out{(__bf16*)a.o, a.lse, a.part_o, a.part_lse, a.total_q, 0};
   const PackedSizes sizes{a.max_q, a.max_k, a.total_q, a.total_k};
-  auto kern = a.n_split == 1 ? (a.small ? attn_varlen_kernel<D, kFinal, true> : attn_varlen_kernel<D, kFinal, false>)
-                             : (a.small ? attn_varlen_kernel<D, kPartial, true> : attn_varlen_kernel<D, kPartial, false>);
+  auto kern = a.small           ? (a.n_split == 1 ? attn_varlen_kernel<D, kFinal, true, false>
+                                                  : attn_varlen_kernel<D, kPartial, true, false>)
+              : a.scale == 0.0f ? (a.n_split == 1 ? attn_varlen_kernel<D, kFinal, false, true>
+                                                  : attn_varlen_kernel<D, kPartial, false, true>)
+                                : (a.n_split == 1 ? attn_varlen_kernel<D, kFinal, false, false>
+                                                  : attn_varlen_kernel<D, kPartial, false, false>);
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads),
                      a.small ? SmallGeo<D>::kLds : Geo<D>::kLds, st, (const __bf16*)a.q,
                      (const __bf16*)a.k, (const __bf16*)a.v, out, a.cu_q, a.cu_k, a.plan, a.nseq, sizes,
@@ -1975,13 +1983,16 @@ static hipError_t configure_d() {
   const struct {
     const void* kern;
     int lds;
-  } all[] = {{(const void*)attn_dense_kernel<D, false>, Geo<D>::kLds},
-             {(const void*)attn_dense_kernel<D, true>, Geo<D>::kLds},
+  } all[] = {{(const void*)attn_dense_kernel<D, false, false>, Geo<D>::kLds},
+             {(const void*)attn_dense_kernel<D, true, false>, Geo<D>::kLds},
+             {(const void*)attn_dense_kernel<D, true, true>, Geo<D>::kLds},
              {(const void*)attn_dense_small_kernel<D>, SmallGeo<D>::kLds},
-             {(const void*)attn_varlen_kernel<D, kFinal, false>, Geo<D>::kLds},
-             {(const void*)attn_varlen_kernel<D, kFinal, true>, SmallGeo<D>::kLds},
-             {(const void*)attn_varlen_kernel<D, kPartial, false>, Geo<D>::kLds},
-             {(const void*)attn_varlen_kernel<D, kPartial, true>, SmallGeo<D>::kLds}};
+             {(const void*)attn_varlen_kernel<D, kFinal, false, false>, Geo<D>::kLds},
+             {(const void*)attn_varlen_kernel<D, kFinal, false, true>, Geo<D>::kLds},
+             {(const void*)attn_varlen_kernel<D, kFinal, true, false>, SmallGeo<D>::kLds},
+             {(const void*)attn_varlen_kernel<D, kPartial, false, false>, Geo<D>::kLds},
+             {(const void*)attn_varlen_kernel<D, kPartial, false, true>, Geo<D>::kLds},
+             {(const void*)attn_varlen_kernel<D, kPartial, true, false>, SmallGeo<D>::kLds}};
   for (const auto& k : all) {
     const hipError_t e =
         hipFuncSetAttribute(k.kern, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds);

@@ -214,9 +214,9 @@ bool no_valid_offsets(const tsattn::PackedArgs& a) {
   return a.nseq == 1 && (a.total_q > a.max_q || a.total_k > a.max_k);
 }
 
-// Whether the call's query tiles are 64 queries (a.n_split is set).
+// Whether the call's query tiles are 64 queries (a.n_split is set).  Scale 0 has 256-query kernels only.
 bool small_tiles(const tsattn::PackedArgs& a, int32_t cus) {
-  return tsattn::small_items(
+  return a.scale != 0.0f && tsattn::small_items(
       tsattn::packed_items(a.total_q, a.nseq, a.H, a.n_split, tsattn::kSmallTile), a.max_k, cus);
 }
 
@@ -400,7 +400,7 @@ int ts_attn_fwd(const void* q, const void* k, const void* v, void* o, int32_t B,
   if (!st) return rc;
   const int64_t small = (int64_t)B * H * ((L + tsattn::kSmallTile - 1) / tsattn::kSmallTile);
   tsattn::DenseArgs a{q, k, v, o, B, L, H, d, scale, st->xcd_chunk,
-                      tsattn::small_items(small, L, st->cus)};
+                      scale != 0.0f && tsattn::small_items(small, L, st->cus)};
   return tsattn::launch_dense(a, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 

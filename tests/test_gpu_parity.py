@@ -187,6 +187,30 @@ def test_other_scales_full(scale, seqlens):
     assert_rows(as_f64(o), ref, "scale=%g %r" % (scale, seqlens), elementwise=False)
 
 
+# items of 64 and of 256 queries, full and thin, of one key tile and of several; `at`: the key's place
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L,H", [(20, 2), (100, 2), (700, 2), (700, 40), (276, 2), (276, 100)])
+def test_infinite_scores_at_scale_zero(L, H, d):
+    # the scores' products with scale 0 are 0, and NaN where a score is infinite, whatever its sign
+    g = torch.Generator().manual_seed(L + d)
+    q, k, v = (torch.randn((1, L, H, d), generator=g).to(torch.bfloat16) for _ in range(3))
+    q[:, :, 0, 0] = 1.0
+    q[:, ::2, 0, 0] = -1.0
+    want = v.float().mean(dim=1, keepdim=True)
+    for at in (0, L // 2, L - 1):
+        kk = k.clone()
+        kk[0, at, 0, 0] = float("inf")
+        for scale in (0.0, -0.0):
+            say("infinite scores at scale", scale, L, H, d, at)
+            o = ts.ts_attn_fwd(q.cuda(), kk.cuda(), v.cuda(), scale=scale)
+            torch.cuda.synchronize()
+            o = o.float().cpu()
+            assert bool(torch.isnan(o[:, :, 0]).all()), (at, scale)
+            # equal weights: only the output is rounded, to 2^-9 of it
+            err = (o[:, :, 1:] - want[:, :, 1:]).abs() - want[:, :, 1:].abs() * 2.0 ** -8
+            assert float(err.max()) <= 1e-6, (at, scale)
+
+
 @pytest.mark.parametrize("seqlens", [[1500, 700], [1560, 280]])
 def test_peaked_scores_full(seqlens):
     # scores 8x larger than N(0,1) inputs give: softmax rows dominated by a few keys, and the
