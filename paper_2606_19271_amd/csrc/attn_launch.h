@@ -89,6 +89,8 @@ struct CopyList {
   int32_t n;
 };
 int64_t copy_chunk_bytes(bool src_host);
+// Whether a device-to-device copy of that size takes non-temporal accesses.
+bool bypass_caches(int64_t bytes);
 // src_host / dst_host: that side is pinned host memory.
 hipError_t launch_state_copy(const void* src, void* dst, const CopyList& list, bool src_host,
                              bool dst_host, hipStream_t st);

@@ -54,4 +54,10 @@ int64_t plan_ints(int32_t nseq) { return 2 + 2 * (int64_t)nseq; }
 
 int64_t copy_chunk_bytes(bool src_host) { return src_host ? kHostReadChunkBytes : kCopyChunkBytes; }
 
+// Up to 128 MiB, read and written 256 MiB, the Infinity Cache holds a copy for the call that reads it
+// next.  Copy alone, and with attention over the copied keys and values after it (us, plain and
+// non-temporal): 40 MiB 13.1 and 14.5, 46.4 and 51.7; 96 MiB 29.5 and 32.6, 80.7 and 89.8; 128 MiB 39.0
+// and 43.5, 103.6 and 113.5; 160 MiB 59.2 and 54.2, 124.6 and 134.4; 256 MiB 92.9 and 86.7, 209 and 203.
+bool bypass_caches(int64_t bytes) { return bytes > (int64_t)128 << 20; }
+
 }  // namespace tsattn

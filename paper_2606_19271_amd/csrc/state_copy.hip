@@ -13,10 +13,10 @@
 // space is dense: a prefix over the ranges' chunk counts maps a chunk to its range.  Pinned host
 // memory is reached directly at its (unified) virtual address.  What bounds each direction, measured
 // on 200 MB to 1.8 GB:
-//  * device -> device, HBM: chunks of 16 KiB, one per workgroup, non-temporal on both sides (the data
-//    is larger than the caches): 6.2 TB/s read + written.  Chunks of 32 KiB reach 4.2-4.4 TB/s with or
-//    without non-temporal accesses, 16 KiB with plain ones 5.7.  Copies of up to 32 MiB, which the
-//    caches hold for the next reader, keep plain accesses.
+//  * device -> device, HBM: chunks of 16 KiB, one per workgroup, non-temporal on both sides where the
+//    data is larger than the caches: 5.9 TB/s read + written.  Chunks of 32 KiB reach 4.2-4.4 TB/s with
+//    or without non-temporal accesses, 16 KiB with plain ones 5.7.  Copies that the caches hold for
+//    the next reader keep plain accesses (bypass_caches).
 //  * device -> host, the link's writes: 32 workgroups walk the chunks together, so that the link sees
 //    nearly consecutive writes: 55.6 GB/s, against 53.6 with a workgroup per chunk, whose order the
 //    dispatcher scatters (8 workgroups 51.4, 16 55.0, 24 55.7, 48 55.3, 256 52.4).  Each loads its
@@ -128,8 +128,8 @@ hipError_t launch_state_copy(const void* src, void* dst, const CopyList& list, b
   }
   auto kern = src_host ? (dst_host ? tsstate::state_copy_kernel<kLarge, true, true>
                                    : tsstate::state_copy_kernel<kLarge, true, false>)
-              : chunks * kCopyChunkBytes > ((int64_t)32 << 20) ? tsstate::state_copy_kernel<kSmall, true, true>
-                                                               : tsstate::state_copy_kernel<kSmall, false, false>;
+              : bypass_caches(chunks * kCopyChunkBytes) ? tsstate::state_copy_kernel<kSmall, true, true>
+                                                        : tsstate::state_copy_kernel<kSmall, false, false>;
   // a grid holds fewer than 2^32 threads: 2^23 chunks a launch, 128 GiB of 16 KiB ones
   constexpr int64_t kLaunch = (int64_t)1 << 23;
   for (int64_t first = 0; first < chunks; first += kLaunch) {

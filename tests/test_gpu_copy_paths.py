@@ -1,6 +1,6 @@
 """State copies at the sizes where the kernels change: the 16 KiB and 32 KiB chunk edges, fewer and
 more chunks than the workgroups of a suspend walk, and device-to-device copies on both sides of the
-32 MiB from which they are non-temporal; against the range copy by definition, bit for bit."""
+128 MiB from which they are non-temporal; against the range copy by definition, bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -22,7 +22,8 @@ def gpu():
 @pytest.mark.parametrize("where", ["dev->host", "host->dev", "dev->dev"])
 @pytest.mark.parametrize("sizes", [[16], [16 * K - 16, 16 * K, 16 * K + 16], [32 * K - 16, 32 * K + 16, 0, 48 * K],
                                    [512 * K, 512 * K + 16], [3 << 20, 16, 5 * K], [(32 << 20) - 4 * 16 * K, 16],
-                                   [(32 << 20) + 16, 16 * K + 48, 0, 1 << 20]], ids=str)
+                                   [(32 << 20) + 16, 16 * K + 48, 0, 1 << 20], [(128 << 20) - 2 * 16 * K, 16],
+                                   [128 << 20, 32]], ids=str)
 def test_copy_paths(where, sizes):
     print("[gpu-test] copy", where, sizes, flush=True)
     src_at, dst_at = where.split("->")

@@ -1,5 +1,6 @@
-"""The library's choice of key ranges and item size for chunk calls (csrc/attn_plan.cpp, host code),
-compiled with g++ under ASan and UBSan with a driver that walks random and extreme shapes."""
+"""The library's host-side choices (csrc/attn_plan.cpp): key ranges, item size and plan of packed and
+chunk calls, accesses of device copies; compiled with g++ under ASan and UBSan with a driver that walks
+random and extreme shapes."""
 import os
 import shutil
 import subprocess
@@ -59,6 +60,8 @@ int main() {
   CHECK(wave_plan(1, 1 << 23, 256) && wave_plan(64, 1, 256) && wave_plan(64, 384, 256) && !wave_plan(64, 385, 256));
   CHECK(!wave_plan(65, 1, 256) && !wave_plan(64, 2560, 256) && !wave_plan(32, 1280, 256) && !wave_plan(48, 1920, 256));
   CHECK(wave_plan(8, 1280, 256) && wave_plan(2, 12288, 256) && !wave_plan(2, 12289, 256) && !wave_plan(64, 1 << 23, 256));
+  // device copies: plain accesses as long as the Infinity Cache holds what is read and written
+  CHECK(!bypass_caches(40ll << 20) && !bypass_caches(128ll << 20) && bypass_caches((128ll << 20) + 1));
   printf("failures %d\n", bad);
   return bad != 0;
 }
