@@ -3,7 +3,7 @@
 Each case is a dense batch, a packed batch, or a chunk-vs-cache batch (allocating, or allocating
 and allocation-free on the same arguments), with segment lengths drawn around the 256-query
 tile, the 32-query thin tile, the 16-key blocks and the key tiles (64 keys at d = 128, 128 at
-d = 64), one segment half of the time (the call then runs without the planning kernel), and
+d = 64), one segment half of the time (so few segments run without the planning kernel), and
 random heads, head width, scale (zero and negative included), score peaking (q x 1, 4, 8) and
 split count.  Bars: those of every other parity test (tests/metrics.py, per-row relative bar
 included; the element bar is left to the long-segment tests, see metrics.assert_rows), lse within

@@ -68,8 +68,8 @@ def test_dense_call_replays_from_a_graph(d):
     assert torch.equal(bits(again), bits(refs[1]))
 
 
-# (segments of queries, segments of keys, H, d, num_splits): several segments (planning kernel),
-# one segment (no planning kernel), split key ranges (merge kernel), the library's split choice
+# (segments of queries, segments of keys, H, d, num_splits): several segments, one segment (neither
+# needs the planning kernel), split key ranges (merge kernel), the library's split choice
 GRAPH_CASES = [
     ((300, 0, 129), None, 2, 128, 1),
     ((1000,), None, 2, 64, 1),

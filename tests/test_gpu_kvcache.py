@@ -219,7 +219,7 @@ def test_kv_workload_sampled(name, n_random):
 
 
 def test_kv_rejected_offsets_leave_outputs_untouched():
-    # a rejected plan is a no-op on every path: also with split key ranges, where the merge
+    # rejected offsets are a no-op on every path: also with split key ranges, where the merge
     # kernel must not write O or lse from partials that were never computed
     w, q, k, v = draw([64, 64], [128, 128], 1, 64, 92)
     cq = torch.tensor(w.cu_q, device="cuda")
@@ -236,8 +236,8 @@ def test_kv_rejected_offsets_leave_outputs_untouched():
 
 @pytest.mark.parametrize("splits", [1, 3])
 def test_kv_one_segment_bad_offsets_are_noops(splits):
-    # A call of one segment runs without the planning kernel: the attention and merge kernels
-    # check its offsets against {0, total} themselves.  Offsets that do not start at 0 or do not
+    # A call of few segments runs without the planning kernel: the attention and merge kernels
+    # check its offsets themselves, of one segment against {0, total}.  Offsets that do not start at 0 or do not
     # end at the tensors' rows leave O and lse untouched; so do totals beyond max_seqlen, which
     # the host turns away before any device work; and validation mode still reports them.
     w, q, k, v = draw([64], [128], 1, 64, 93)

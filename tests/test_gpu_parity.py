@@ -404,7 +404,7 @@ def test_bad_cu_seqlens_is_a_noop_and_validate_mode_reports_it():
     finally:
         del os.environ["TS_ATTN_VALIDATE"]
     torch.cuda.synchronize()
-    # outside validation mode a batch of one segment runs without the planning kernel; bad
+    # outside validation mode a batch of few segments runs without the planning kernel; bad
     # offsets (not ending at the row count, or not starting at 0) or a total beyond max_seqlen
     # still leave o untouched
     for cu_l, max_len in (([0, 200], 300), ([100, 300], 300), ([0, 300], 100)):

@@ -1,5 +1,5 @@
-"""Calls that cannot fill the GPU run in 64-query items, others in 256-query ones, and batches of at
-most 64 segments are planned by the attention kernel itself, others by a planning kernel.  Neither
+"""Calls that cannot fill the GPU run in 64-query items, others in 256-query ones, and batches of up to
+64 segments in few items are planned by the attention kernel itself, others by a planning kernel.  Neither
 choice may change a bit of a row's result: the same sequences are computed alone and in a batch large
 enough to change the path.  The small path is checked against the fp64 oracle as well.
 """
