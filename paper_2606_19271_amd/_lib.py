@@ -70,7 +70,8 @@ def i32s(**sizes):
 
 
 def current_stream(device):
-    """torch's current stream of a GPU device as a hipStream_t value."""
+    """torch's current stream of a GPU device as a hipStream_t value.  The public
+    torch.cuda.current_stream(device) builds a Stream object around it: 1.85 us a call against 0.09."""
     return torch._C._cuda_getCurrentRawStream(device.index)
 
 

@@ -32,8 +32,9 @@
 //    tile's maximum taken and the O accumulator rescaled.  Keeping a stale maximum is exact in
 //    real arithmetic (the final division by the running sum cancels the common factor), so for
 //    ordinary inputs the per-tile max reduction and the O rescale disappear.
-//  * A call with fewer items than a quarter of the CUs runs in 64-query items instead, whose key tiles
-//    are split over the eight waves (run_small_item), with the same results bit for bit.
+//  * A call of so few queries that all its 64-query items run at once, one per CU (small_items), runs in
+//    those, whose key tiles are split over the eight waves (run_small_item), with the same results bit
+//    for bit.
 //  * Scheduling: the launch has one workgroup per item; blockIdx is remapped so that the 32
 //    workgroups resident at once on one XCD (the hardware deals workgroups to the 8 XCDs
 //    round robin) take 32 consecutive query tiles of the same head and share its K/V in that
@@ -952,7 +953,7 @@ __device__ __forceinline__ void run_thin_item(const Item& it, const __bf16* __re
 
   // Q fragments (B operand of the 16x16x32 S MFMAs): query i16 of block qb, channels
   // 32 kk + 8 g + 0..7.  Loaded between the first two fetches, and its sign flipped after the wait
-  // (as in the main schedule, no use of Q delays a fetch).
+  // (so that no use of Q delays a fetch).
   const int qrow = it.q_begin + 16 * qb + i16;
   fetch(0, 0);
   u32x4 qraw[D / 32];
@@ -1077,7 +1078,7 @@ __device__ __forceinline__ void run_thin_item(const Item& it, const __bf16* __re
   typedef __attribute__((address_space(3))) float lds_float;
   lds_float* const obuf = (lds_float*)lds;
   lds_f32x2* const mlbuf = (lds_f32x2*)(lds + kWaves * 16 * D * 4);
-  static_assert(kWaves * 16 * D * 4 + kWaves * 16 * 8 <= G::kLds, "combine buffer fits the rings");
+  static_assert(kWaves * 16 * D * 4 + kWaves * 16 * 8 <= G::kRings, "combine buffer fits the rings");
 #pragma unroll
   for (int cb = 0; cb < kCB; ++cb)
     *(lds_f32x4*)(obuf + (wave * 16 + i16) * D + 16 * cb + 4 * g) = o[cb];
@@ -1146,8 +1147,9 @@ __device__ __forceinline__ void run_thin_item(const Item& it, const __bf16* __re
 
 // ---- Small grids: 64-query items, every K/V tile shared by the eight waves.
 //
-// With fewer 256-query items than CUs a call is one chain of key tiles, each as long as a matrix
-// step and a vector step of a whole wave, while most of the chip idles.  Here a workgroup takes 64
+// Where a call has fewer 256-query items than CUs it is one chain of key tiles, each as long as a matrix
+// step and a vector step of a whole wave, while part of the chip idles.  Where its 64-query items do not
+// outnumber the CUs either (small_items), it runs in those.  Here a workgroup takes 64
 // queries (two blocks of 32) and splits a key tile's work over its waves instead:
 //  * Waves 0-3, the producers, compute the scores and weights: a score block is 32 keys x 32
 //    queries, an accumulator as in the main schedule.  At d = 128 producer w has keys
@@ -1239,7 +1241,7 @@ __device__ __forceinline__ void run_small_item(const Item& it, const __bf16* __r
     return fmaxf(m_c, __builtin_fmaf(mt, c, kBias));
   };
 
-  // prologue: the queries (64 rows, 1 KiB per instruction, in the weight buffers), K_0 .. K_2, V_0
+  // prologue: the queries (64 rows, 1 KiB per instruction, in the weight buffers), K_0 .. K_3, V_0
   int koff[G::kKDmaMax], voff[G::kVDmaPerWave];
   // The first barrier waits for the queries and K_0 only, the second for K_1 and K_2, phase 0 for the rest
   // (all of it before the first barrier: three 256-query chunks at d = 64 14.67 us against 14.51, 1024

@@ -22,7 +22,9 @@ int64_t packed_items(int32_t total_q, int32_t nseq, int32_t H, int32_t n_split, 
 // takes 0.5 to 0.7 of a 256-query item's (measured, 1024 keys: 11.3 against 17.5 us for 16 heads at
 // d = 64, 14.9 against 21.6 at d = 128; 256 keys x 4 heads 5.9 against 8.2 and 6.6 against 9.5).  In
 // two rounds they lose: 18 heads 20.3 against 17.5 us and 26.1 against 21.6.  Up to 64 keys there is
-// nothing to split (4.65 against 4.7 us at d = 64, 4.8 against 4.4 at d = 128).
+// nothing to split (4.65 against 4.7 us at d = 64, 4.8 against 4.4 at d = 128).  The items of a packed
+// call are counted by packed_items from the totals alone, nearly one too many a segment, head and range, so
+// a batch whose items would fit may still run in 256-query ones.
 bool small_items(int64_t items, int32_t max_k, int32_t cus) { return items <= cus && max_k > 64; }
 
 // A wave's own plan costs each round of items 0.085 us a segment, and saves the planning kernel, 4 to
