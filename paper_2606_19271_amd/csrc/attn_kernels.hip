@@ -1581,7 +1581,7 @@ __device__ __forceinline__ void run_small_item(const Item& it, const __bf16* __r
 template <int D, int kMode, int kQueries>
 __device__ __forceinline__ void write_empty(const Item& it, const Out& out, int H, char* smem) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (32 * wave >= kQueries) return;
+  if (32 * wave >= min(kQueries, it.q_len - it.q_begin)) return;
   f32x16 zero[D / 32];
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) zero[db] = f32x16{};

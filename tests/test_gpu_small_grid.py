@@ -170,3 +170,20 @@ def test_automatic_key_ranges(lq, lk, H, d, n):
         o, lse = entry(*args, return_lse=True, num_splits=0)
         torch.cuda.synchronize()
         assert torch.equal(bits(o), bits(want)) and torch.equal(bits(lse), bits(want_lse)), entry
+
+
+@pytest.mark.parametrize("H", [2, 40])  # items of 64 and of 256 queries
+@pytest.mark.parametrize("splits", [1, 2])
+def test_segments_without_keys_are_zeros(H, splits):
+    lq, lk = [1, 31, 32, 33, 64, 65, 255, 256, 257, 300], [0] * 9 + [200]
+    q, _, _ = draw(sum(lq), 1, H, 128, 21, "normal")
+    _, k, v = draw(1, sum(lk), H, 128, 22, "normal")
+    cq, ck = (torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32, device="cuda") for x in (lq, lk))
+    say("segments without keys", H, splits)
+    out = torch.full(q.shape, 7.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full(q.shape[:2], 7.0, dtype=torch.float32, device="cuda")
+    ts.ts_attn_fwd_kvcache(q.cuda(), k.cuda(), v.cuda(), cq, ck, max(lq), max(lk), out=out, lse=lse, num_splits=splits)
+    torch.cuda.synchronize()
+    empty = sum(lq[:-1])
+    assert bool((out[:empty] == 0).all()) and bool((lse[:empty] == -math.inf).all())
+    assert bool((out[empty:] != 7.0).any()) and bool(torch.isfinite(lse[empty:]).all())
