@@ -1577,11 +1577,13 @@ __device__ __forceinline__ void run_small_item(const Item& it, const __bf16* __r
   }
 }
 
-// An item of kQueries queries without keys: O = 0, lse = -inf.
+// An item of kQueries queries without keys: O = 0, lse = -inf.  Waves whose rows all lie past the segment's
+// end have nothing to write.  (Of a 64-query item's two waves one could leave so; the test for it moved the
+// thin path's loop of these kernels, and 1560 queries x 2 heads took 19.16 instead of 18.87 us.)
 template <int D, int kMode, int kQueries>
 __device__ __forceinline__ void write_empty(const Item& it, const Out& out, int H, char* smem) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (32 * wave >= min(kQueries, it.q_len - it.q_begin)) return;
+  if (32 * wave >= (kQueries == kBM ? min(kQueries, it.q_len - it.q_begin) : kQueries)) return;
   f32x16 zero[D / 32];
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) zero[db] = f32x16{};
